@@ -37,6 +37,8 @@
 // rotated query H diag(sign) q and accumulate values in the rotated domain.
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "semkv_internal.h"
 
 namespace semkv {
@@ -91,7 +93,15 @@ typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kRsqrtD = 0.08838834764831845f;   // 1 / sqrt(128)
-constexpr int kQPad = 160;                         // query rows, zero past channel 127
+
+// f(0), ..., f(N-1) with compile-time indices
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void static_for(F f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, F, I + 1>(f);
+  }
+}
 
 // ------------------------------------------------------------ traits ----
 
@@ -100,6 +110,8 @@ __host__ __device__ constexpr int ipow(int b, int e) {
   for (int i = 0; i < e; ++i) r *= b;
   return r;
 }
+
+__host__ __device__ constexpr int gcd_of(int a, int b) { return b == 0 ? a : gcd_of(b, a % b); }
 
 // Chunk layout: an MFMA operand gives each lane 16 byte slots; a chunk fills
 // them with SPC symbols of STRIDE slots each; slot_digit / slot_plane give the
@@ -512,6 +524,17 @@ struct Geo {
   static constexpr int NG = BASE != 1 ? kD / G : 1;          // score products per chunk (query groups)
   static constexpr int NGV = BASE != 1 ? kD / G : 1;         // value groups
   static constexpr int NPL = Tr::P;                          // value planes (tq, 4 levels: 2)
+  // Score products: a chunk covers CCH consecutive channels, a query group GQ,
+  // so only the (group, chunk) pairs that share a channel are not all zero
+  // (G = 32: 5 of 12 at 5 levels, 7 of 16 at 6).  Pairs are numbered along the
+  // channels; pair_at is the number of the pair that holds channel c: the
+  // chunk and group edges at or below c, each once.
+  static constexpr int CCH = 4 * Tr::SPC * Tr::n, GQ = BASE != 1 ? G : kD;
+  static constexpr int BOTH = CCH / gcd_of(CCH, GQ) * GQ;     // both have an edge at its multiples
+  __host__ __device__ static constexpr int pair_at(int c) { return c / CCH + c / GQ - c / BOTH; }
+  static constexpr int NPAIR = pair_at(kD - 1) + 1;
+  static constexpr bool pair_used(int g, int ch) { return ch * CCH < (g + 1) * GQ && g * GQ < (ch + 1) * CCH; }
+  static constexpr int pair_of(int g, int ch) { return pair_at(g * GQ > ch * CCH ? g * GQ : ch * CCH); }
   // int8 weights of one wave and one value group at a time, in value
   // A-operand order: [chunk][lane group][row][16 slots], so a lane reads a
   // chunk's operand at once.  Row 4h + s holds byte s of head h's weights;
@@ -525,6 +548,19 @@ struct Geo {
   static constexpr int PV = Tr::NCV * CHB;                   // bytes per wave
   static_assert(RB % 16 == 0, "record pieces");
 };
+
+// the pairs in use are numbered 0, 1, ... without gaps, and every channel's
+// pair is the one of its chunk and group
+template <class Ge, int NCK, int NG>
+__host__ __device__ constexpr bool pairs_numbered() {
+  int n = 0;
+  for (int g = 0; g < NG; ++g)
+    for (int ch = 0; ch < NCK; ++ch)
+      if (Ge::pair_used(g, ch)) n += Ge::pair_of(g, ch) < Ge::NPAIR ? 1 : 1000;
+  for (int c = 0; c < kD; ++c)
+    if (!Ge::pair_used(c / Ge::GQ, c / Ge::CCH) || Ge::pair_of(c / Ge::GQ, c / Ge::CCH) != Ge::pair_at(c)) return false;
+  return n == Ge::NPAIR;
+}
 
 template <int CTRL>
 __device__ inline float dpp(float x) {
@@ -590,13 +626,14 @@ struct Plan {
   static constexpr int PV = GH::PV > GL::PV ? GH::PV : GL::PV;
   static constexpr int NGV = GH::NGV;
   static constexpr int NG = GH::NG;
-  static constexpr int NCKH = Traits<BASE, LH>::NCK, NCKL = Traits<BASE, LL>::NCK;
+  static constexpr int NPAIRS = GH::NPAIR + GL::NPAIR;       // score operands of both pools
   static_assert(GH::NGV == GL::NGV, "pools share the value groups");
+  static_assert(pairs_numbered<GH, Traits<BASE, LH>::NCK, GH::NG>() && pairs_numbered<GL, Traits<BASE, LL>::NCK, GL::NG>(), "pairs");
   // LDS of a workgroup of nw waves with rh / rl table replicas (the Shared
   // layout below, with margin)
   static constexpr int lds_bytes(int nw, int rh, int rl) {
     return nw * (NLD * 1024 + PV + 256) + (Traits<BASE, LH>::LUTDW * rh + Traits<BASE, LL>::LUTDW * rl) * 4 +
-           NG * (NCKH + NCKL) * 64 * 16 + 4 * kQPad * 4 + 4 * kD * 4 + 2080 + 3104 + 512;
+           (GH::NPAIR + GL::NPAIR) * 64 * 16 + 4 * kD * 4 + 2080 + 3104 + 640;
   }
   // 8 waves: 2 per SIMD, one workgroup per compute unit.  A level pair whose
   // 8-wave workgroup does not fit is refused by the host.
@@ -632,13 +669,13 @@ struct Shared {
   alignas(16) uint32_t lut[PL::LUTH + PL::LUTL];
   alignas(16) uint8_t stage[PL::NW][PL::NLD * 1024];         // per wave: one record, later its Fin
   alignas(16) uint8_t pv[PL::NW][PL::PV];                    // per wave int8 weights
-  alignas(16) float qf[4][kQPad];                            // fp32 query, rotated for bases 1, 2
   float qorig[4][kD];                                        // query as given (fp16 tail)
   Fin tfin;                                                  // the fp16 tail's state
   TailScratch ts;
-  alignas(16) uint4 aq[PL::NG][PL::NCKH + PL::NCKL][64];     // score A operands, per group, pool and lane
+  alignas(16) uint4 aq[PL::NPAIRS][64];                      // score A operands: pool, (group, chunk) pair, lane
   float zpart[4][4];                                         // per head: sums of q over 32-channel runs
   float qmax[4][4];                                          // per head: max |q| over 32-channel runs
+  float qsc[2][4][4], zws[2][4][4];                          // per pool, head and group: score scale, zero-point term
   float zc[PL::NW][4][4];                                    // per wave, head, group: sum p * zero
   int last;
 };
@@ -750,42 +787,56 @@ __device__ inline int query_exp(const Shared<PL>& sm, const float* mu, int h, in
   return mx >= 1e-30f ? 20 - E : 0;
 }
 
-// Score A operands of one pool for all 64 lane contexts, by the workgroup:
-// for query group g, lane (row m = 4h + s, kg) chunk c slot e holds byte s of
-// qi = rint(x 2^e) at the channel the slot addresses (zero past channel 127,
-// in pad slots, outside group g and in rows 4h + 3), x the query of head h
-// (affine), its rotated query (rotated affine) or its plane-weighted rotated
-// query (tq), |qi| < 2^20.  qi splits
-// as 2^14 b0 + 2^7 b1 + b2 (b0 signed, b1, b2 in [0, 127]), so a product sums
-// the exact integer qi . codes in three rows.
-// Items are dealt to threads from thread OFF on (the low pool's start where
-// the high pool's end), so the two pools' items spread over the workgroup.
-template <int BASE, int L, int G, int POOL, int OFF, class PL>
-__device__ void build_aq(const DecodeArgs& a, Shared<PL>& sm) {
+// Constants of one pool's scores and weights.  tq: mu = -m, 0, m (L = 3) or
+// -b, -a, a, b (L = 4), affine in a code's bit planes.  Rotated affine: k =
+// sign . H y / 8 with y = s c + z the affine value of the rotated coordinates,
+// so q . k = (H sign . q) . y / 8, and the values are summed as y / 8 in the
+// rotated domain (powers of 2: exact).
+template <int BASE, int L>
+struct Scale {
+  static constexpr float kR = BASE == 2 ? 0.125f : 1.0f;
+  static constexpr float kScore = kLog2e * kRsqrtD * kR;
+  float cS, cZ, wP[2];
+  __device__ explicit Scale(const float* mu)
+      : cS(BASE != 1 ? 1.0f : (L == 3 ? mu[2] / 128.0f : 1.0f / 128.0f)),
+        cZ(BASE != 1 ? 0.0f : (L == 3 ? -mu[2] / 128.0f : -mu[3] / 128.0f)),
+        wP{BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[3] - mu[2]), BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[2] + mu[3])} {}
+};
+
+// Score A operands of one pool, by the threads that hold the query x (affine)
+// or the rotated query (bases 1, 2), one per (head h, channel c).  Lane (row m
+// = 4h + s, kg), (group, chunk) pair, slot holds byte s of qi = rint(x 2^e)
+// (tq: of the plane-weighted x) at the channel the slot addresses, |qi| <
+// 2^20, e per head and group.  qi splits as 2^14 b0 + 2^7 b1 + b2 (b0 signed,
+// b1, b2 in [0, 127]), so a product sums the exact integer qi . codes in three
+// rows.  Each thread makes its channel's integer once and writes its three
+// bytes to the one place each has; pad slots and rows 4h + 3 are zero before
+// the call.  Gathering, one thread per operand of 16 slots, repeated the
+// rounding for every slot, byte and group: at G = 32 and 2048 tokens it took
+// 2.1 us of a 12.1 us launch (the scatter: 0.75), at G = 128 0.75 us (0.45).
+// The group's first thread also leaves the score scale 2^-e and the
+// zero-point term (the sum of q) of its head and group.
+template <int BASE, int L, int G, int POOL, class PL>
+__device__ inline void scatter_query(const DecodeArgs& a, Shared<PL>& sm, float x, int h, int c) {
   using Tr = Traits<BASE, L>;
   using Ge = Geo<BASE, L, G>;
-  const float* mu = a.mu[POOL];
-  const float wP[2] = {BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[3] - mu[2]),
-                       BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[2] + mu[3])};
-  for (int item = (int(threadIdx.x) + PL::NT - OFF % PL::NT) % PL::NT; item < Ge::NG * Tr::NCK * 64; item += PL::NT) {
-    const int g = item / (Tr::NCK * 64), c = (item >> 6) % Tr::NCK, ln = item & 63;
-    const int m = ln & 15, kg = ln >> 4, h = m >> 2, sp = m & 3;
-    const int e = query_exp<BASE, L, G>(sm, mu, h, g);
-    // branch free: every slot reads at a clamped channel (all reads in
-    // flight together) and keeps the byte only where the slot is real
-    const int shift = sp == 0 ? 14 : sp == 1 ? 7 : 0;
-    const int bmask = sp == 0 ? 0xFF : 0x7F;
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
+  using Sc = Scale<BASE, L>;
+  const Sc k(a.mu[POOL]);
+  const int g = c / Ge::GQ;
+  const int e = query_exp<BASE, L, G>(sm, a.mu[POOL], h, g);
+  const int p = c / Tr::n, d = c - p * Tr::n, kg = p & 3, sk = p >> 2;
+  uint8_t* dst = reinterpret_cast<uint8_t*>(&sm.aq[(POOL ? PL::GH::NPAIR : 0) + Ge::pair_at(c)][kg * 16 + 4 * h]) +
+                 (sk % Tr::SPC) * Tr::STRIDE + digit_slot<BASE, L>(d);
 #pragma unroll
-    for (int sl = 0; sl < 16; ++sl) {
-      const int k = Tr::SPC * c + sl / Tr::STRIDE, ws = sl % Tr::STRIDE;
-      const int dig = slot_digit<BASE, L>(ws), pl = slot_plane<BASE, L>(ws);
-      const int ch = kg * Tr::n + Tr::n * 4 * k + (dig < 0 ? 0 : dig);      // >= 128: a pad slot
-      const bool ok = dig >= 0 && sp < 3 && ch < kD && (BASE == 1 || ch / G == g);
-      const int qi = int(rintf(ldexpf(wP[pl] * sm.qf[h][ch < kD ? ch : 0], e)));
-      w[sl >> 2] |= (ok ? uint32_t((qi >> shift) & bmask) : 0u) << (8 * (sl & 3));
-    }
-    sm.aq[g][(POOL ? PL::NCKH : 0) + c][ln] = make_uint4(w[0], w[1], w[2], w[3]);
+  for (int pl = 0; pl < Tr::P; ++pl) {
+    const int qi = int(rintf(ldexpf(k.wP[pl] * x, e)));
+    dst[pl] = uint8_t(qi >> 14);
+    dst[pl + 16] = uint8_t((qi >> 7) & 0x7F);
+    dst[pl + 32] = uint8_t(qi & 0x7F);
+  }
+  if (c % Ge::GQ == 0) {
+    sm.qsc[POOL][h][g] = ldexpf(Sc::kScore * (BASE != 1 ? 1.0f : k.cS), -e);
+    sm.zws[POOL][h][g] = query_sum<BASE, G>(sm, h, g) * (Sc::kScore * (BASE != 1 ? 1.0f : k.cZ));
   }
 }
 
@@ -801,27 +852,20 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, r = lane >> 4, kg = r;
   uint8_t* rec = sm.stage[wave];
-  // tq: mu = -m, 0, m (L = 3) or -b, -a, a, b (L = 4)
-  const float* mu = a.mu[POOL];
-  const float cS = BASE != 1 ? 1.0f : (L == 3 ? mu[2] / 128.0f : 1.0f / 128.0f);
-  const float cZ = BASE != 1 ? 0.0f : (L == 3 ? -mu[2] / 128.0f : -mu[3] / 128.0f);
-  const float wP[2] = {BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[3] - mu[2]),
-                       BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[2] + mu[3])};
-  // rotated affine: k = sign . H y / 8 with y = s c + z the affine value of
-  // the rotated coordinates, so q . k = (H sign . q) . y / 8, and the values
-  // are summed as y / 8 in the rotated domain (powers of 2: exact)
-  constexpr float kR = BASE == 2 ? 0.125f : 1.0f;
-  constexpr float kScore = kLog2e * kRsqrtD * kR;
+  const Scale<BASE, L> sc(a.mu[POOL]);
+  constexpr float kR = Scale<BASE, L>::kR;
 
   // ---- score A operands (built once per workgroup): in registers for one
   // query group, else read per product
+  constexpr int A0 = POOL ? PL::GH::NPAIR : 0;
+  auto aq = [&](int pair) {
+    const uint4 v = sm.aq[A0 + pair][lane];
+    return __builtin_bit_cast(int4v, uint4v{v.x, v.y, v.z, v.w});
+  };
   int4v Aq[NG == 1 ? Tr::NCK : 1];
   if constexpr (NG == 1) {
 #pragma unroll
-    for (int c = 0; c < Tr::NCK; ++c) {
-      const uint4 v = sm.aq[0][(POOL ? PL::NCKH : 0) + c][lane];
-      Aq[c] = __builtin_bit_cast(int4v, uint4v{v.x, v.y, v.z, v.w});
-    }
+    for (int c = 0; c < Tr::NCK; ++c) Aq[c] = aq(c);
   }
   // tables: the lane's replica; entries 2^S bytes apart
   constexpr int NR = POOL ? PL::RL : PL::RH;
@@ -845,8 +889,8 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
   float zwsK[NG], qscK[NG];
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
-    zwsK[i] = query_sum<BASE, G>(sm, r, i) * (kScore * (BASE != 1 ? 1.0f : cZ));
-    qscK[i] = ldexpf(kScore * (BASE != 1 ? 1.0f : cS), -query_exp<BASE, L, G>(sm, mu, r, i));
+    zwsK[i] = sm.zws[POOL][r][i];
+    qscK[i] = sm.qsc[POOL][r][i];
   }
   // softmax lanes: where token 16 blk + n of each block lands in the weight
   // operands (value group 0, plane 0, row 4r)
@@ -886,11 +930,19 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
       for (int i = 0; i < NKM; ++i)
         km[blk][i] = BASE != 1 ? *reinterpret_cast<const uint32_t*>(kmeta + (i * kSlots + t) * 4)
                                : uint32_t(*reinterpret_cast<const uint16_t*>(kmeta + t * 2));
-#pragma unroll
-      for (int i = 0; i < NVM; ++i)
-        vm[blk][i] = BASE != 1 ? *reinterpret_cast<const uint32_t*>(vmeta + (i * kSlots + t) * 4)
-                               : uint32_t(*reinterpret_cast<const uint16_t*>(vmeta + t * 2));
     }
+    // the value metadata too, or, with many words of it, only after the scores
+    auto load_vm = [&]() {
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk) {
+        const int t = 16 * blk + n;
+#pragma unroll
+        for (int i = 0; i < NVM; ++i)
+          vm[blk][i] = BASE != 1 ? *reinterpret_cast<const uint32_t*>(vmeta + (i * kSlots + t) * 4)
+                                 : uint32_t(*reinterpret_cast<const uint16_t*>(vmeta + t * 2));
+      }
+    };
+    if constexpr (NVM == 1) load_vm();
     // the score of token 16 blk + n from its products, one per query group,
     // in the softmax's base-2 scale: (q . c) 2^-e s + z (sum q) per group
     // (tq: rho ((q . c) 2^-e cS + cZ sum q)); masked tokens are set apart
@@ -918,21 +970,20 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
       if (blk + 1 < 4) chunk_operands<BASE, L, S, KFULL, Tr::KSEGW, Tr::NSK, Tr::NCK>(kseg[blk + 1], kmask, lut, Bk[(blk + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
       int4v acc[NG];
-#pragma unroll
-      for (int i = 0; i < NG; ++i) {
+      static_for<NG>([&](auto I) {
+        constexpr int i = I.value;
         acc[i] = int4v{0, 0, 0, 0};
-#pragma unroll
-        for (int ch = 0; ch < Tr::NCK; ++ch) {
-          int4v A;
-          if constexpr (NG == 1) {
-            A = Aq[ch];
-          } else {
-            const uint4 v = sm.aq[i][(POOL ? PL::NCKH : 0) + ch][lane];
-            A = __builtin_bit_cast(int4v, uint4v{v.x, v.y, v.z, v.w});
+        static_for<Tr::NCK>([&](auto C) {
+          constexpr int ch = C.value;
+          if constexpr (Ge::pair_used(i, ch)) {              // else chunk ch holds no channel of group i
+            int4v A;
+            constexpr int pair = Ge::pair_of(i, ch);
+            if constexpr (NG == 1) A = Aq[ch];
+            else A = aq(pair);
+            acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, Bk[blk & 1][ch], acc[i], 0, 0, 0);
           }
-          acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, Bk[blk & 1][ch], acc[i], 0, 0, 0);
-        }
-      }
+        });
+      });
       if constexpr (DEFER) {
 #pragma unroll
         for (int i = 0; i < NG; ++i) acck[blk][i] = acc[i];
@@ -943,6 +994,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
     }
     // the value segments and the first value operands do not depend on the
     // softmax: their LDS round trips overlap it
+    if constexpr (NVM > 1) load_vm();
     const uint8_t* vbody = rec + Tr::TB;
     uint32_t vseg[8][Tr::VSEGW];
 #pragma unroll
@@ -989,10 +1041,10 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
         const float rho = hf(uint16_t(vm[blk][0]));
 #pragma unroll
         for (int pl = 0; pl < Ge::NPL; ++pl) {
-          wv[blk][0][pl] = p * rho * cS * wP[pl];
+          wv[blk][0][pl] = p * rho * sc.cS * sc.wP[pl];
           wmax = fmaxf(wmax, wv[blk][0][pl]);
         }
-        zadd[0] = fmaf(p * rho, cZ, zadd[0]);
+        zadd[0] = fmaf(p * rho, sc.cZ, zadd[0]);
       }
     }
     // ---- the integer value sums hold weights of one scale and one reference
@@ -1403,6 +1455,7 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
     for (int k = 0; k < NTL; ++k)
       if (tid + k * NT < PL::LUTL / 4) d[PL::LUTH / 4 + tid + k * NT] = tl[k];
   }
+  for (int i = tid; i < PL::NPAIRS * 64; i += NT) (&sm.aq[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
   SEMKV_STAMP_FINE(19);
   float xq = 0.0f;
   if (qt) {
@@ -1413,14 +1466,14 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   SEMKV_STAMP_FINE(20);
   if (BASE != 0) xq = fwht_rows(xq, sm.ts.o);    // rotate: H (sign . q)
   if (qt) {
-    sm.qf[h][c] = xq;
-    if (c < kQPad - kD) sm.qf[h][kD + c] = 0.0f;
     query_runs(xq, h, c, sm);                   // the query the scores use: its runs
   }
   SEMKV_STAMP_FINE(21);
   __syncthreads();
-  build_aq<BASE, LH, G, 0, 0>(a, sm);
-  build_aq<BASE, LL, G, 1, PL::GH::NG * PL::NCKH * 64>(a, sm);
+  if (qt) {
+    scatter_query<BASE, LH, G, 0>(a, sm, xq, h, c);
+    scatter_query<BASE, LL, G, 1>(a, sm, xq, h, c);
+  }
   __syncthreads();
   SEMKV_STAMP(1);
 

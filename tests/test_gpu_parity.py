@@ -190,6 +190,19 @@ def test_other_affine_level_pairs(levels):
     _check_decode(cache, cfgw, 500, flags, [0])
 
 
+@pytest.mark.parametrize("G", [32, 64])
+@pytest.mark.parametrize("base,levels", [("affine", (6, 5)), ("affine", (5, 4)), ("affine", (6, 4)), ("affine", (4, 3)),
+                                         ("affine", (5, 3)), ("affine", (6, 3)), ("rot_affine", (6, 5)),
+                                         ("rot_affine", (5, 4))])
+def test_score_products_of_every_level_pair_and_group(base, levels, G):
+    """With metadata groups finer than a row only the products whose channels
+    meet the group are computed; which those are depends on the levels of each
+    pool and on the group."""
+    cfgw = get_config(0, base=base, L_hi=levels[0], L_lo=levels[1], n_kv_heads=1, n_q_heads=4, group=G, r_num=1, r_den=2)
+    cache, flags = _check_prefill(cfgw, 131)
+    _check_decode(cache, cfgw, 131, flags, [0])
+
+
 def test_turboquant_base_small():
     cfgw = get_config(4, n_layers=2, n_kv_heads=2, n_q_heads=8)
     cache, flags = _check_prefill(cfgw, 1500, n_layers=2)
