@@ -7,9 +7,13 @@
 // u mod (nsplit NW), slot v = w nsplit + s being wave w of workgroup s.  Every
 // wave thus gets an even share of the (costlier) high-precision tiles, first
 // in its sequence, and keeps its own online-softmax state for the 4 query
-// heads of the kv head.  Records are staged through registers: the next record's
-// 16-byte pieces are loaded while the current one is computed from the wave's
-// LDS buffer, then written over it.  Products run on the int8 matrix cores
+// heads of the kv head.  Each lane loads the segments it decodes from memory
+// straight into its registers, a record ahead; only a record's metadata goes
+// through LDS.  (With whole records staged in LDS the staging writes, the
+// unaligned segment reads and their bank conflicts were a third of the LDS
+// cycles, 518 a record at batch 16, and LDS was active 61 % of the time: batch
+// 16 at 16384 tokens 47.7 -> 42.6 us a launch, batch 4 at 32768 31.4 -> 29.2,
+// tq at 131072 25.6 -> 24.9.)  Products run on the int8 matrix cores
 // (v_mfma_i32_16x16x64_i8), exact in their integer sums.  Per record:
 //   scores  C[16 rows (head, byte) x 16 tokens] += A B: A holds the query of
 //           head h as a fixed-point integer qi = rint(q 2^e) (|qi| < 2^20, e
@@ -298,18 +302,47 @@ static_assert(entries_match_digits<0, 6>() && entries_match_digits<0, 5>() && en
               entries_match_digits<0, 3>() && entries_match_digits<1, 4>() && entries_match_digits<1, 3>() &&
               entries_match_digits<0, 2>() && entries_match_digits<0, 7>() && entries_match_digits<0, 8>(), "tables");
 
+// A pool's decode table and the places of its weights, made by the compiler
+// and read from memory by every workgroup: made by the workgroup instead, the
+// table took 110 of a launch's ~530 prologue instructions per wave.
+//  lut:  the table's dwords, entry after entry (one copy)
+//  pvw:  per lane (n, r): where the weights of tokens 16 blk + n, blk = 0..3,
+//        land in the weight operands (value group 0, plane 0, row 4r)
+constexpr int kLaneGroup = 16 * 16 + 16;                     // bytes per lane group of the weight operands
+template <int BASE, int L>
+struct PoolConst {
+  using Tr = Traits<BASE, L>;
+  uint32_t lut[Tr::LUTDW];
+  uint32_t pvw[64][4];
+  constexpr PoolConst() : lut(), pvw() {
+    for (int e = 0; e < Tr::NENT; ++e) {
+      lut[e * Tr::TED] = entry_dword<BASE, L, 0>(uint32_t(e));
+      if (Tr::TED == 2) lut[e * Tr::TED + Tr::TED - 1] = entry_dword<BASE, L, 1>(uint32_t(e));
+    }
+    for (int lane = 0; lane < 64; ++lane)
+      for (int blk = 0; blk < 4; ++blk) {
+        const int t = 16 * blk + lane % 16, p = t / Tr::n, d = t % Tr::n, k = p / 4;
+        pvw[lane][blk] = uint32_t((k / Tr::SPC) * 4 * kLaneGroup + p % 4 * kLaneGroup + 64 * (lane / 16) +
+                                  k % Tr::SPC * Tr::STRIDE + digit_slot<BASE, L>(d));
+      }
+  }
+};
+template <int BASE, int L>
+__device__ const PoolConst<BASE, L> kPoolConst{};
+
 // 16-byte piece q of the replicated LDS table (entry e of replica r at entry
 // slot e R + r; R >= 4, so a piece lies in one entry, repeated)
 template <int BASE, int L, int R>
 __device__ inline uint4 lut_piece(uint32_t q) {
   using Tr = Traits<BASE, L>;
   static_assert(R >= 4 && (R & (R - 1)) == 0, "replicas");
+  const uint32_t* t = kPoolConst<BASE, L>.lut;
   if constexpr (Tr::TED == 1) {
-    const uint32_t x = entry_dword<BASE, L, 0>((4 * q) / R);
+    const uint32_t x = t[(4 * q) / R];
     return make_uint4(x, x, x, x);
   } else {
-    const uint32_t E = (2 * q) / R, x = entry_dword<BASE, L, 0>(E), y = entry_dword<BASE, L, 1>(E);
-    return make_uint4(x, y, x, y);
+    const uint2 x = *reinterpret_cast<const uint2*>(t + 2 * ((2 * q) / R));
+    return make_uint4(x.x, x.y, x.x, x.y);
   }
 }
 
@@ -500,17 +533,17 @@ __device__ inline void segment_masks(int j, uint32_t (&mask)[NS]) {
                     (1u << t.width[2][k]) - 1u, (1u << t.width[3][k]) - 1u);
 }
 
-// first bit of line `line` in segment j, and the bits one line of it takes
+// dwords that hold any line's segment, from the dword of its first bit on
 template <int L, int NVALS, int NLINES>
-__device__ inline int seg_off(int j, int line) {
+__host__ __device__ constexpr int seg_dwords() {
   constexpr SegTable<L, NVALS, NLINES> t{};
-  return pick4(j, t.start[0], t.start[1], t.start[2], t.start[3]) +
-         line * pick4(j, t.bits[0], t.bits[1], t.bits[2], t.bits[3]);
-}
-template <int L, int NVALS, int NLINES>
-__device__ inline int seg_line_bits(int j) {
-  constexpr SegTable<L, NVALS, NLINES> t{};
-  return pick4(j, t.bits[0], t.bits[1], t.bits[2], t.bits[3]);
+  int most = 0;
+  for (int j = 0; j < 4; ++j)
+    for (int line = 0; line < NLINES; ++line) {
+      const int n = ((t.start[j] + line * t.bits[j]) % 32 + t.bits[j] + 31) / 32;
+      most = n > most ? n : most;
+    }
+  return most;
 }
 
 __device__ inline float hf(uint16_t b) { return __half2float(__ushort_as_half(b)); }
@@ -520,7 +553,8 @@ struct Geo {
   using Tr = Traits<BASE, L>;
   static constexpr int MB = meta_bytes(BASE, G);
   static constexpr int RB = 2 * Tr::TB + 2 * MB;
-  static constexpr int NLD = (RB + 1023) / 1024;            // 1 KB staging pieces per record
+  static constexpr int KLD = seg_dwords<L, kD, kSlots>(), VLD = seg_dwords<L, kSlots, kD>();   // dwords of a segment
+  static constexpr int NML = (2 * MB + 1023) / 1024;         // 1 KB metadata pieces per record
   static constexpr int NG = BASE != 1 ? kD / G : 1;          // score products per chunk (query groups)
   static constexpr int NGV = BASE != 1 ? kD / G : 1;         // value groups
   static constexpr int NPL = Tr::P;                          // value planes (tq, 4 levels: 2)
@@ -543,7 +577,7 @@ struct Geo {
   // lane groups 272 bytes apart (16 rows of 16 slots, then 16 bytes of pad):
   // the byte writes of consecutive symbols, which sit in consecutive lane
   // groups, land in different LDS banks rather than all in one
-  static constexpr int KGS = 16 * 16 + 16;                   // bytes per lane group
+  static constexpr int KGS = kLaneGroup;                     // bytes per lane group
   static constexpr int CHB = 4 * KGS;                        // bytes per chunk
   static constexpr int PV = Tr::NCV * CHB;                   // bytes per wave
   static_assert(RB % 16 == 0, "record pieces");
@@ -604,16 +638,12 @@ __device__ inline float row_sum16(float x) {
   return x + dpp<0x121>(x);
 }
 
-// LDS-staged segment: NW dwords starting at bit `bitoff` of an LDS body
-template <int NW>
-__device__ inline void lds_segment(const uint8_t* body, int bitoff, uint32_t (&seg)[NW]) {
-  const uint32_t* p = reinterpret_cast<const uint32_t*>(body) + (bitoff >> 5);
-  uint32_t r[NW + 1];
+// normalized segment of NW dwords from the ND dwords that hold it, the first
+// bit at bit `sh` (its low 5 bits) of the first
+template <int NW, int ND>
+__device__ inline void normalize(const uint32_t* d, int sh, uint32_t (&seg)[NW]) {
 #pragma unroll
-  for (int k = 0; k <= NW; ++k) r[k] = p[k];
-  const int sh = bitoff & 31;
-#pragma unroll
-  for (int k = 0; k < NW; ++k) seg[k] = __builtin_amdgcn_alignbit(r[k + 1], r[k], sh);
+  for (int k = 0; k < NW; ++k) seg[k] = __builtin_amdgcn_alignbit(k + 1 < ND ? d[k + 1] : 0u, k < ND ? d[k] : 0u, sh);
 }
 
 // ------------------------------------------------------- kernel layout ----
@@ -622,7 +652,8 @@ template <int BASE, int LH, int LL, int G>
 struct Plan {
   using GH = Geo<BASE, LH, G>;
   using GL = Geo<BASE, LL, G>;
-  static constexpr int NLD = GH::NLD > GL::NLD ? GH::NLD : GL::NLD;
+  static constexpr int KLD = GH::KLD > GL::KLD ? GH::KLD : GL::KLD, VLD = GH::VLD > GL::VLD ? GH::VLD : GL::VLD;
+  static constexpr int NML = GH::NML;
   static constexpr int PV = GH::PV > GL::PV ? GH::PV : GL::PV;
   static constexpr int NGV = GH::NGV;
   static constexpr int NG = GH::NG;
@@ -632,7 +663,7 @@ struct Plan {
   // LDS of a workgroup of nw waves with rh / rl table replicas (the Shared
   // layout below, with margin)
   static constexpr int lds_bytes(int nw, int rh, int rl) {
-    return nw * (NLD * 1024 + PV + 256) + (Traits<BASE, LH>::LUTDW * rh + Traits<BASE, LL>::LUTDW * rl) * 4 +
+    return nw * (NML * 1024 + PV + 2112 + 256) + (Traits<BASE, LH>::LUTDW * rh + Traits<BASE, LL>::LUTDW * rl) * 4 +
            (GH::NPAIR + GL::NPAIR) * 64 * 16 + 4 * kD * 4 + 2080 + 3104 + 640;
   }
   // 8 waves: 2 per SIMD, one workgroup per compute unit.  A level pair whose
@@ -655,6 +686,9 @@ struct Plan {
   }
   static constexpr int RH = pick_replicas(true), RL = pick_replicas(false);
   static_assert(RH >= 4 && RL >= 4, "LDS");
+  // table entries are 2^SH, 2^SL bytes apart
+  static constexpr int SH = ilog2(RH * Traits<BASE, LH>::TED * 4), SL = ilog2(RL * Traits<BASE, LL>::TED * 4);
+  static_assert((1 << SH) == RH * Traits<BASE, LH>::TED * 4 && (1 << SL) == RL * Traits<BASE, LL>::TED * 4, "entry stride");
   static constexpr int LUTH = Traits<BASE, LH>::LUTDW * RH;  // dwords of the high-pool tables
   static constexpr int LUTL = Traits<BASE, LL>::LUTDW * RL;
 };
@@ -662,12 +696,21 @@ struct Plan {
 struct Fin { float m[4], l[4]; float o[4][kD]; };             // one wave's state, merged form
 struct TailScratch { float lg[4][kSlots]; float mx[4], sum[4]; float o[4][kD]; };
 
+// A wave's current record in registers: the dwords of its lanes' four K
+// segments and eight V segments, and the metadata on its way to LDS.
+template <class PL>
+struct Record {
+  uint32_t k[4][PL::KLD], v[8][PL::VLD];
+  uint4 m[PL::NML];
+};
+
 template <class PL>
 struct Shared {
   // decode tables (high pool, low pool) first: their offsets fit the 16-bit
   // immediate offset of an LDS read, so a lookup needs no base add
   alignas(16) uint32_t lut[PL::LUTH + PL::LUTL];
-  alignas(16) uint8_t stage[PL::NW][PL::NLD * 1024];         // per wave: one record, later its Fin
+  alignas(16) uint8_t meta[PL::NW][PL::NML * 1024];          // per wave: the record's metadata
+  alignas(16) Fin fin[PL::NW];                               // per wave: its state when its records are done
   alignas(16) uint8_t pv[PL::NW][PL::PV];                    // per wave int8 weights
   float qorig[4][kD];                                        // query as given (fp16 tail)
   Fin tfin;                                                  // the fp16 tail's state
@@ -679,9 +722,6 @@ struct Shared {
   float zc[PL::NW][4][4];                                    // per wave, head, group: sum p * zero
   int last;
 };
-
-template <class PL>
-__device__ inline Fin* wave_fin(Shared<PL>& sm, int w) { return reinterpret_cast<Fin*>(sm.stage[w]); }
 
 template <int NGV>
 struct WaveState {
@@ -718,30 +758,119 @@ __device__ inline float comb3_score(const int4v& c) {
   return float((t << 7) + c[2]);
 }
 
-// ---------------------------------------------------------- staging ----
+// ------------------------------------------------------- record loads ----
 
-// piece j of lane l is bytes [1024 j + 16 l, +16) of a record, read through a
-// buffer descriptor bounded by the record's size: pieces past its end read 0
-// without touching memory, so every record takes the same NMAX loads
+// Where a lane's segments of a record of one pool begin: byte offsets of the
+// first two blocks' dwords, the bytes from a block to the next but one, and the
+// bit within (32 lines are a whole number of dwords, so blocks two apart share
+// it).
+struct LaneGeo {
+  int kb[2], vb[2], kstep, vstep, ksh[2], vsh[2];
+};
 
-template <int BASE, int LH, int LL, int G, int NMAX>
-__device__ inline void load_tile(const PoolGeom& g, const uint8_t* unit, int tile, int nt0, uint4 (&r)[NMAX], int lane) {
-  using PL = Plan<BASE, LH, LL, G>;
-  const bool hi = tile < nt0;
-  const int rb = hi ? PL::GH::RB : PL::GL::RB;
-  const uint8_t* rec = hi ? unit + int64_t(tile) * PL::GH::RB : unit + g.lo_offset + int64_t(tile - nt0) * PL::GL::RB;
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(rec), 0, rb, kBufferWord3);
+// What a lane's geometry needs of the segments of one body, in scalars: bits
+// of a line's segment j in byte j of `bits`, and the bits of the segments
+// before it as j b0 less byte j of `less`.
+struct SegScalars {
+  uint32_t bits, less;
+  int b0;
+};
+template <int L, int NV, int NL>
+__host__ __device__ constexpr SegScalars seg_scalars() {
+  constexpr SegTable<L, NV, NL> t{};
+  SegScalars s{0u, 0u, t.bits[0]};
+  for (int j = 0; j < 4; ++j) {
+    s.bits |= uint32_t(t.bits[j]) << (8 * j);
+    s.less |= uint32_t(j * t.bits[0] - t.start[j] / NL) << (8 * j);
+  }
+  return s;
+}
+template <int L, int NV, int NL>
+__host__ __device__ constexpr bool seg_scalars_ok() {
+  constexpr SegTable<L, NV, NL> t{};
+  for (int j = 0; j < 4; ++j) {
+    const int less = j * t.bits[0] - t.start[j] / NL;
+    if (t.bits[j] < 0 || t.bits[j] > 255 || less < 0 || less > 255 || t.start[j] % NL != 0) return false;
+  }
+  return true;
+}
+
+// the lane's geometry in the high (hi) or low pool: hi is the same for the
+// whole wave, so the pool's constants are scalar selects (about 35 vector
+// instructions; every wave pays them before its first record's loads)
+template <int BASE, int LH, int LL>
+__device__ inline LaneGeo lane_geo(bool hi, int lane) {
+  static_assert(seg_scalars_ok<LH, kD, kSlots>() && seg_scalars_ok<LL, kD, kSlots>() && seg_scalars_ok<LH, kSlots, kD>() &&
+                seg_scalars_ok<LL, kSlots, kD>(), "segment scalars");
+  constexpr SegScalars kH = seg_scalars<LH, kD, kSlots>(), kL = seg_scalars<LL, kD, kSlots>();
+  constexpr SegScalars vH = seg_scalars<LH, kSlots, kD>(), vL = seg_scalars<LL, kSlots, kD>();
+  const uint32_t n = lane & 15, j = lane >> 4;
+  // first bit of line n's segment j, and the bits of one line of it
+  auto first = [&](uint32_t bits, uint32_t less, int b0, int lines, int& lb) {
+    lb = int(__builtin_amdgcn_ubfe(bits, 8 * j, 8));
+    return int(__umul24(j, b0) - __builtin_amdgcn_ubfe(less, 8 * j, 8)) * lines + int(__umul24(n, lb));
+  };
+  int kbits, vbits;
+  const int k0 = first(hi ? kH.bits : kL.bits, hi ? kH.less : kL.less, hi ? kH.b0 : kL.b0, kSlots, kbits);
+  const int v0 = first(hi ? vH.bits : vL.bits, hi ? vH.less : vL.less, hi ? vH.b0 : vL.b0, kD, vbits) +
+                 8 * (hi ? tile_bytes(LH) : tile_bytes(LL));
+  LaneGeo g;
+  g.ksh[0] = k0;
+  g.ksh[1] = k0 + 16 * kbits;
+  g.vsh[0] = v0;
+  g.vsh[1] = v0 + 16 * vbits;
 #pragma unroll
-  for (int j = 0; j < NMAX; ++j) {
-    const uint4v v = __builtin_amdgcn_raw_buffer_load_b128(rs, j * 1024 + lane * 16, 0, 0);
-    r[j] = make_uint4(v.x, v.y, v.z, v.w);
+  for (int i = 0; i < 2; ++i) {
+    g.kb[i] = (g.ksh[i] >> 3) & ~3;
+    g.vb[i] = (g.vsh[i] >> 3) & ~3;
+  }
+  g.kstep = 4 * kbits;
+  g.vstep = 4 * vbits;
+  return g;
+}
+
+template <int N>
+__device__ inline void load_dwords(__amdgpu_buffer_rsrc_t rs, int off, uint32_t* r) {
+  if constexpr (N >= 4) {
+    const uint4v x = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+    r[0] = x.x, r[1] = x.y, r[2] = x.z, r[3] = x.w;
+    load_dwords<N - 4>(rs, off + 16, r + 4);
+  } else if constexpr (N == 3) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b96(rs, off, 0, 0);
+    r[0] = x[0], r[1] = x[1], r[2] = x[2];
+  } else if constexpr (N == 2) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+    r[0] = x[0], r[1] = x[1];
+  } else if constexpr (N == 1) {
+    r[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
   }
 }
 
-template <int NMAX>
-__device__ inline void store_pieces(const uint4 (&r)[NMAX], uint8_t* lds, int lane) {
+// Loads a record straight into the registers that use it: each lane the
+// dwords of its own segments, through a buffer descriptor bounded by the
+// record's size (what a load reads past its end is 0, without memory traffic).
+// Every record takes the same loads, whichever its pool; with `any` false
+// (no record is left) they are bounded by 0 bytes and read nothing.
+template <int BASE, int LH, int LL, int G, class PL>
+__device__ inline void load_record(const PoolGeom& g, const uint8_t* unit, int tile, int nt0, bool any, const LaneGeo& lg,
+                                   Record<PL>& r, int lane) {
+  const bool hi = tile < nt0;
+  const uint8_t* rec = hi ? unit + int64_t(tile) * PL::GH::RB : unit + g.lo_offset + int64_t(tile - nt0) * PL::GL::RB;
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(rec), 0, !any ? 0 : hi ? PL::GH::RB : PL::GL::RB, kBufferWord3);
 #pragma unroll
-  for (int j = 0; j < NMAX; ++j) *reinterpret_cast<uint4*>(lds + j * 1024 + lane * 16) = r[j];
+  for (int i = 0; i < 4; ++i) load_dwords<PL::KLD>(rs, lg.kb[i & 1] + (i >> 1) * lg.kstep, r.k[i]);
+#pragma unroll
+  for (int i = 0; i < PL::NML; ++i) {
+    const uint4v x = __builtin_amdgcn_raw_buffer_load_b128(rs, (hi ? 2 * tile_bytes(LH) : 2 * tile_bytes(LL)) + i * 1024 + lane * 16, 0, 0);
+    r.m[i] = make_uint4(x.x, x.y, x.z, x.w);
+  }
+  int vb[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    vb[i] = i < 2 ? lg.vb[i] : vb[i - 2] + lg.vstep;
+    load_dwords<PL::VLD>(rs, vb[i], r.v[i]);
+  }
 }
 
 // Per head, of the query x (affine) or the rotated query (bases 1, 2) held by one
@@ -817,26 +946,46 @@ struct Scale {
 // The group's first thread also leaves the score scale 2^-e and the
 // zero-point term (the sum of q) of its head and group.
 template <int BASE, int L, int G, int POOL, class PL>
-__device__ inline void scatter_query(const DecodeArgs& a, Shared<PL>& sm, float x, int h, int c) {
+__device__ inline void scatter_bytes(Shared<PL>& sm, int qi, int h, int c, int pl) {
   using Tr = Traits<BASE, L>;
   using Ge = Geo<BASE, L, G>;
-  using Sc = Scale<BASE, L>;
-  const Sc k(a.mu[POOL]);
-  const int g = c / Ge::GQ;
-  const int e = query_exp<BASE, L, G>(sm, a.mu[POOL], h, g);
   const int p = c / Tr::n, d = c - p * Tr::n, kg = p & 3, sk = p >> 2;
   uint8_t* dst = reinterpret_cast<uint8_t*>(&sm.aq[(POOL ? PL::GH::NPAIR : 0) + Ge::pair_at(c)][kg * 16 + 4 * h]) +
-                 (sk % Tr::SPC) * Tr::STRIDE + digit_slot<BASE, L>(d);
+                 (sk % Tr::SPC) * Tr::STRIDE + digit_slot<BASE, L>(d) + pl;
+  dst[0] = uint8_t(qi >> 14);
+  dst[16] = uint8_t((qi >> 7) & 0x7F);
+  dst[32] = uint8_t(qi & 0x7F);
+}
+template <int BASE, int LH, int LL, int G, class PL>
+__device__ inline void scatter_query(const DecodeArgs& a, Shared<PL>& sm, float x, int h, int c) {
+  constexpr int GQ = PL::GH::GQ;
+  const int g = c / GQ;
+  if constexpr (BASE != 1) {                 // the same integers and scales in both pools
+    const int e = query_exp<BASE, LH, G>(sm, a.mu[0], h, g);
+    const float z = query_sum<BASE, G>(sm, h, g);
+    const int qi = int(rintf(ldexpf(x, e)));
+    scatter_bytes<BASE, LH, G, 0>(sm, qi, h, c, 0);
+    scatter_bytes<BASE, LL, G, 1>(sm, qi, h, c, 0);
+    if (c % GQ == 0) {
+      const float k = Scale<BASE, LH>::kScore;
+      sm.qsc[0][h][g] = sm.qsc[1][h][g] = ldexpf(k, -e);
+      sm.zws[0][h][g] = sm.zws[1][h][g] = z * k;
+    }
+  } else {
+    auto pool = [&](auto I) {
+      constexpr int POOL = I.value, L = POOL ? LL : LH;
+      using Sc = Scale<BASE, L>;
+      const Sc k(a.mu[POOL]);
+      const int e = query_exp<BASE, L, G>(sm, a.mu[POOL], h, g);
 #pragma unroll
-  for (int pl = 0; pl < Tr::P; ++pl) {
-    const int qi = int(rintf(ldexpf(k.wP[pl] * x, e)));
-    dst[pl] = uint8_t(qi >> 14);
-    dst[pl + 16] = uint8_t((qi >> 7) & 0x7F);
-    dst[pl + 32] = uint8_t(qi & 0x7F);
-  }
-  if (c % Ge::GQ == 0) {
-    sm.qsc[POOL][h][g] = ldexpf(Sc::kScore * (BASE != 1 ? 1.0f : k.cS), -e);
-    sm.zws[POOL][h][g] = query_sum<BASE, G>(sm, h, g) * (Sc::kScore * (BASE != 1 ? 1.0f : k.cZ));
+      for (int pl = 0; pl < Traits<BASE, L>::P; ++pl)
+        scatter_bytes<BASE, L, G, POOL>(sm, int(rintf(ldexpf(k.wP[pl] * x, e))), h, c, pl);
+      if (c % GQ == 0) {
+        sm.qsc[POOL][h][g] = ldexpf(Sc::kScore * k.cS, -e);
+        sm.zws[POOL][h][g] = query_sum<BASE, G>(sm, h, g) * (Sc::kScore * k.cZ);
+      }
+    };
+    static_for<2>(pool);
   }
 }
 
@@ -844,14 +993,15 @@ __device__ inline void scatter_query(const DecodeArgs& a, Shared<PL>& sm, float 
 
 template <int BASE, int LH, int LL, int G, int POOL, class PL>
 __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>& st, const uint8_t* unit,
-                         int nt0, int first, int stride, int i0, int i1, int count, uint4 (&R)[PL::NLD]) {
+                         int nt0, int first, int stride, int i0, int i1, int count, Record<PL>& R, LaneGeo& geo, uint4& pvwq) {
   constexpr int L = POOL ? LL : LH;
   using Tr = Traits<BASE, L>;
   using Ge = Geo<BASE, L, G>;
   constexpr int NG = Ge::NG, NGV = Ge::NGV;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, r = lane >> 4, kg = r;
-  uint8_t* rec = sm.stage[wave];
+  uint8_t* kmeta = sm.meta[wave];
+  const uint8_t* vmeta = kmeta + Ge::MB;
   const Scale<BASE, L> sc(a.mu[POOL]);
   constexpr float kR = Scale<BASE, L>::kR;
 
@@ -869,8 +1019,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
   }
   // tables: the lane's replica; entries 2^S bytes apart
   constexpr int NR = POOL ? PL::RL : PL::RH;
-  constexpr int S = ilog2(NR * Tr::TED * 4);
-  static_assert((1 << S) == NR * Tr::TED * 4, "entry stride");
+  constexpr int S = POOL ? PL::SL : PL::SH;
   constexpr uint32_t KFULL = full_symbols<L, kD, kSlots>(), VFULL = full_symbols<L, kSlots, kD>();
   const uint32_t lb = uint32_t((lane & (NR - 1)) * Tr::TED * 4);
   const LutRef lut{reinterpret_cast<const uint8_t*>(sm.lut + (POOL ? PL::LUTH : 0)), lb, lb + (uint32_t(Tr::DIV) << S)};
@@ -881,8 +1030,10 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
   for (int k = 0; k < Tr::NSK; ++k) kmask[k] <<= S;
 #pragma unroll
   for (int k = 0; k < Tr::NSV; ++k) vmask[k] <<= S;
-  const int koff0 = seg_off<L, kD, kSlots>(kg, n), kstep = 16 * seg_line_bits<L, kD, kSlots>(kg);
-  const int voff0 = seg_off<L, kSlots, kD>(kg, n), vstep = 16 * seg_line_bits<L, kSlots, kD>(kg);
+  // softmax lanes: where token 16 blk + n of each block lands in the weight
+  // operands (value group 0, plane 0, row 4r)
+  if (POOL == 1 && i0 > 0) pvwq = *reinterpret_cast<const uint4*>(kPoolConst<BASE, L>.pvw[lane]);
+  const uint32_t pvwr[4] = {pvwq.x, pvwq.y, pvwq.z, pvwq.w};
   // softmax lanes: token n of each 16-token block, head r.  Per query group
   // of head r, times the softmax scale: the sum of q (zero-point term) and
   // 2^-e (the fixed-point query's scale); tq folds its level offsets in
@@ -892,46 +1043,57 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
     zwsK[i] = sm.zws[POOL][r][i];
     qscK[i] = sm.qsc[POOL][r][i];
   }
-  // softmax lanes: where token 16 blk + n of each block lands in the weight
-  // operands (value group 0, plane 0, row 4r)
+  // the weight operands' pad slots and unused rows are zero: cleared by the
+  // prologue, and again where the low pool's layout follows the high pool's
   uint8_t* pvw = sm.pv[wave];
-  int pvwr[4];
-#pragma unroll
-  for (int blk = 0; blk < 4; ++blk) {
-    const int t = 16 * blk + n, p = t / Tr::n, d = t - p * Tr::n, k = p >> 2;
-    pvwr[blk] = (k / Tr::SPC) * Ge::CHB + (p & 3) * Ge::KGS + 64 * r + (k % Tr::SPC) * Tr::STRIDE + digit_slot<BASE, L>(d);
-  }
   static_assert(Ge::PV % 16 == 0, "weight array pieces");
-  for (int i = lane; i < Ge::PV / 16; i += 64) reinterpret_cast<uint4*>(pvw)[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (POOL == 1 && i0 > 0)
+    for (int i = lane; i < Ge::PV / 16; i += 64) reinterpret_cast<uint4*>(pvw)[i] = make_uint4(0u, 0u, 0u, 0u);
   const int64_t nrows = a.n_rows[POOL];
 
   for (int it = i0; it < i1; ++it) {
     const int tile = first + stride * it;
-    const bool more = it + 1 < count;
-    if (more) load_tile<BASE, LH, LL, G>(a.g, unit, tile + stride, nt0, R, lane);
+    // this record's segments and metadata out of the load registers, then
+    // the next record's loads into them
+    uint32_t kseg[4][Tr::KSEGW], vseg[8][Tr::VSEGW];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) normalize<Tr::KSEGW, Ge::KLD>(R.k[i], geo.ksh[i & 1], kseg[i]);
+#pragma unroll
+    for (int i = 0; i < PL::NML; ++i) *reinterpret_cast<uint4*>(kmeta + i * 1024 + lane * 16) = R.m[i];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) normalize<Tr::VSEGW, Ge::VLD>(R.v[i], geo.vsh[i & 1], vseg[i]);
+    // (the empty statements keep the extraction here: sunk below the loads,
+    // it would need a second set of load registers)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < Tr::KSEGW; ++k) __asm__ volatile("" : "+v"(kseg[i][k]));
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int k = 0; k < Tr::VSEGW; ++k) __asm__ volatile("" : "+v"(vseg[i][k]));
+    if (POOL == 0 && it + 1 == i1) geo = lane_geo<BASE, LH, LL>(false, lane);     // the next one is the low pool's
+    load_record<BASE, LH, LL, G>(a.g, unit, tile + stride, nt0, it + 1 < count, geo, R, lane);
     if (it == 0) SEMKV_STAMP_FINE(16);
     const int ptile = POOL ? tile - nt0 : tile;
-    const uint8_t* kmeta = rec + 2 * Tr::TB;
-    const uint8_t* vmeta = kmeta + Ge::MB;
     const int nvalid = nrows - int64_t(ptile) * kSlots < kSlots ? int(nrows - int64_t(ptile) * kSlots) : kSlots;
 
     // ---- scores: C[(h, byte)][token] = q_h bytes . codes; lane holds token n, head r
     float lg[4];
-    // all four K segments and the lane's metadata words in one round trip
-    uint32_t kseg[4][Tr::KSEGW];
-#pragma unroll
-    for (int blk = 0; blk < 4; ++blk) lds_segment<Tr::KSEGW>(rec, koff0 + blk * kstep, kseg[blk]);
+    // metadata written above by other lanes of this wave
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     constexpr int NKM = BASE != 1 ? NG : 1, NVM = BASE != 1 ? NGV : 1;
     uint32_t km[4][NKM], vm[4][NVM];
-#pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
+    auto load_km = [&](int blk) {
       const int t = 16 * blk + n;
 #pragma unroll
       for (int i = 0; i < NKM; ++i)
         km[blk][i] = BASE != 1 ? *reinterpret_cast<const uint32_t*>(kmeta + (i * kSlots + t) * 4)
                                : uint32_t(*reinterpret_cast<const uint16_t*>(kmeta + t * 2));
-    }
-    // the value metadata too, or, with many words of it, only after the scores
+    };
+    // one metadata word a token: all read here; several: a block's keys' words
+    // with its products, the values' after the scores
     auto load_vm = [&]() {
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
@@ -942,7 +1104,11 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
                                  : uint32_t(*reinterpret_cast<const uint16_t*>(vmeta + t * 2));
       }
     };
-    if constexpr (NVM == 1) load_vm();
+    if constexpr (NVM == 1) {
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk) load_km(blk);
+      load_vm();
+    }
     // the score of token 16 blk + n from its products, one per query group,
     // in the softmax's base-2 scale: (q . c) 2^-e s + z (sum q) per group
     // (tq: rho ((q . c) 2^-e cS + cZ sum q)); masked tokens are set apart
@@ -967,6 +1133,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
     int4v acck[DEFER ? 4 : 1][NG];
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
+      if constexpr (NVM > 1) load_km(blk);
       if (blk + 1 < 4) chunk_operands<BASE, L, S, KFULL, Tr::KSEGW, Tr::NSK, Tr::NCK>(kseg[blk + 1], kmask, lut, Bk[(blk + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
       int4v acc[NG];
@@ -992,13 +1159,9 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    // the value segments and the first value operands do not depend on the
-    // softmax: their LDS round trips overlap it
+    // the first value operands do not depend on the softmax: their LDS round
+    // trip overlaps it
     if constexpr (NVM > 1) load_vm();
-    const uint8_t* vbody = rec + Tr::TB;
-    uint32_t vseg[8][Tr::VSEGW];
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) lds_segment<Tr::VSEGW>(vbody, voff0 + cb * vstep, vseg[cb]);
     int4v Bv[2][Tr::NCV];
     chunk_operands<BASE, L, S, VFULL, Tr::VSEGW, Tr::NSV, Tr::NCV>(vseg[0], vmask, lut, Bv[0]);
     if constexpr (DEFER) {
@@ -1113,12 +1276,9 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
       for (int c = 0; c < Tr::NCV; ++c) st.cv[cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(Aw[c], Bv[cb & 1][c], st.cv[cb], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // the next record replaces this one in the wave's buffer (LDS serves a
-    // wave's accesses in order: the reads above come first)
 #ifdef SEMKV_TIMELINE
     if (it == 0) SEMKV_STAMP(8);
 #endif
-    if (more) store_pieces(R, rec, lane);
     SEMKV_STAMP(3 + (it < 4 ? it : 4));
   }
 }
@@ -1140,7 +1300,7 @@ __device__ void wave_finish(Shared<PL>& sm, WaveState<PL::NGV>& st) {
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  Fin* f = wave_fin(sm, wave);
+  Fin* f = &sm.fin[wave];
   if (n == 0) {
     f->m[r] = st.m;
     f->l[r] = st.l;
@@ -1359,8 +1519,8 @@ __device__ void merge_splits(const DecodeArgs& a, Shared<PL>& sm, int vb, int la
     M = Mn;
   }
   struct Quarters { float m[4][4], l[4][4]; float4v o[4][4][32]; };
-  static_assert(sizeof(Quarters) <= sizeof(sm.stage), "merge scratch");
-  Quarters& qs = *reinterpret_cast<Quarters*>(&sm.stage[0][0]);
+  static_assert(sizeof(Quarters) <= sizeof(sm.fin), "merge scratch");
+  Quarters& qs = *reinterpret_cast<Quarters*>(&sm.fin[0]);
   if (mine) {
     if (cq == 0) {
       qs.m[h][q] = M;
@@ -1401,7 +1561,7 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   // blockIdx.z = (layer of the launch) x batch + sequence: an all-layers
   // launch covers n_layers_launched layers from a.layer
   const int split = blockIdx.x, kvh = blockIdx.y, vb = blockIdx.z;
-  const int li = vb / a.g.batch, b = vb - li * a.g.batch, layer = a.layer + li;
+  const int li = a.n_layers_launched > 1 ? vb / a.g.batch : 0, b = vb - li * a.g.batch, layer = a.layer + li;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const PoolGeom& g = a.g;
   SEMKV_STAMP(0);
@@ -1427,25 +1587,32 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
     dst[w] = src[w];
   }
 
-  // ---- this wave's tiles: first, first + stride, ... (high pool first),
-  // and the first of them in flight (a wave without records loads tile 0,
-  // unused)
-  const int nt0 = int((a.n_rows[0] + kSlots - 1) / kSlots), nt1 = int((a.n_rows[1] + kSlots - 1) / kSlots);
-  const int nt = nt0 + nt1, stride = a.nsplit * NW;
-  const int first = wave * a.nsplit + split;
-  const int count = first < nt ? (nt - first + stride - 1) / stride : 0;
-  const int nhi = first < nt0 ? (nt0 - first + stride - 1) / stride : 0;
-  const uint8_t* unit = g.pools + unit_offset(g, b, layer, kvh);
-  uint4 R[PL::NLD];
-  load_tile<BASE, LH, LL, G>(g, unit, count > 0 ? first : 0, nt0, R, lane);
-
-  // ---- decode tables (the query and the first record are in flight)
+  // ---- decode tables, from memory (before the record's loads, so that they
+  // are not waited for with it)
   constexpr int NTH = (PL::LUTH / 4 + NT - 1) / NT, NTL = (PL::LUTL / 4 + NT - 1) / NT;
   uint4 th[NTH], tl[NTL];
+  // the operands' pad slots and unused rows are zero
+  for (int i = tid; i < PL::NPAIRS * 64; i += NT) (&sm.aq[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int i = tid; i < int(sizeof(sm.pv)) / 16; i += NT) reinterpret_cast<uint4*>(&sm.pv[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
   for (int k = 0; k < NTH; ++k) th[k] = lut_piece<BASE, LH, PL::RH>(tid + k * NT < PL::LUTH / 4 ? tid + k * NT : 0);
 #pragma unroll
   for (int k = 0; k < NTL; ++k) tl[k] = lut_piece<BASE, LL, PL::RL>(tid + k * NT < PL::LUTL / 4 ? tid + k * NT : 0);
+  // ---- this wave's tiles: first, first + stride, ... (high pool first),
+  // and the first of them in flight (a wave without records loads tile 0,
+  // unused)
+  const int nt0 = a.tiles[0], stride = a.nsplit * NW;
+  const int first = wave * a.nsplit + split;
+  const int count = a.full[1] + (first < a.left[1] ? 1 : 0), nhi = a.full[0] + (first < a.left[0] ? 1 : 0);
+  const uint8_t* unit = g.pools + unit_offset(g, b, layer, kvh);
+  const int tile0 = count > 0 ? first : 0;
+  // where the softmax lanes' weights go in the wave's first pool
+  uint4 pvwq = *reinterpret_cast<const uint4*>(nhi > 0 ? kPoolConst<BASE, LH>.pvw[lane] : kPoolConst<BASE, LL>.pvw[lane]);
+  LaneGeo geo = {};
+  if (count > 0) geo = lane_geo<BASE, LH, LL>(tile0 < nt0, lane);
+  Record<PL> R;
+  load_record<BASE, LH, LL, G>(g, unit, tile0, nt0, count > 0, geo, R, lane);
+
   {
     uint4* d = reinterpret_cast<uint4*>(sm.lut);
 #pragma unroll
@@ -1455,7 +1622,6 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
     for (int k = 0; k < NTL; ++k)
       if (tid + k * NT < PL::LUTL / 4) d[PL::LUTH / 4 + tid + k * NT] = tl[k];
   }
-  for (int i = tid; i < PL::NPAIRS * 64; i += NT) (&sm.aq[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
   SEMKV_STAMP_FINE(19);
   float xq = 0.0f;
   if (qt) {
@@ -1470,10 +1636,7 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   }
   SEMKV_STAMP_FINE(21);
   __syncthreads();
-  if (qt) {
-    scatter_query<BASE, LH, G, 0>(a, sm, xq, h, c);
-    scatter_query<BASE, LL, G, 1>(a, sm, xq, h, c);
-  }
+  if (qt) scatter_query<BASE, LH, LL, G>(a, sm, xq, h, c);
   __syncthreads();
   SEMKV_STAMP(1);
 
@@ -1489,10 +1652,9 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
     st.of[cb] = 0.0f;
     st.cv[cb] = int4v{0, 0, 0, 0};
   }
-  if (count > 0) store_pieces(R, sm.stage[wave], lane);
   SEMKV_STAMP(2);
-  if (nhi > 0) run_pool<BASE, LH, LL, G, 0>(a, sm, st, unit, nt0, first, stride, 0, nhi, count, R);
-  if (count > nhi) run_pool<BASE, LH, LL, G, 1>(a, sm, st, unit, nt0, first, stride, nhi, count, count, R);
+  if (nhi > 0) run_pool<BASE, LH, LL, G, 0>(a, sm, st, unit, nt0, first, stride, 0, nhi, count, R, geo, pvwq);
+  if (count > nhi) run_pool<BASE, LH, LL, G, 1>(a, sm, st, unit, nt0, first, stride, nhi, count, count, R, geo, pvwq);
   SEMKV_STAMP(9);
 #ifdef SEMKV_TIMELINE
   timeline_put(14, uint32_t(st.nflush));
@@ -1511,12 +1673,12 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   if (qt) {
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, wave_fin(sm, w)->m[h]);
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, sm.fin[w].m[h]);
     if (tail) M = fmaxf(M, sm.tfin.m[h]);
     float Lsum = 0.0f, o = 0.0f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const Fin* f = wave_fin(sm, w);
+      const Fin* f = &sm.fin[w];
       const float sc = f->m[h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(f->m[h] - M);
       Lsum += f->l[h] * sc;
       o += f->o[h][c] * sc;
@@ -1579,8 +1741,19 @@ int launch_g(const DecodeArgs& a, hipStream_t st) {
   if constexpr (!fits<BASE, LH, LL, G>()) {
     return -2;
   } else {
+    using PL = Plan<BASE, LH, LL, G>;
+    // slot s of stride = nsplit x NW holds tiles s, s + stride, ...: their
+    // number, all and of the high pool, without a division in every wave
+    DecodeArgs d = a;
+    const int stride = a.nsplit * PL::NW;
+    d.tiles[0] = int((a.n_rows[0] + kSlots - 1) / kSlots);
+    d.tiles[1] = d.tiles[0] + int((a.n_rows[1] + kSlots - 1) / kSlots);
+    for (int i = 0; i < 2; ++i) {
+      d.full[i] = d.tiles[i] / stride;
+      d.left[i] = d.tiles[i] % stride;
+    }
     dim3 grid(a.nsplit, a.g.n_kv_heads, a.g.batch * a.n_layers_launched);
-    hipLaunchKernelGGL((decode_kernel<BASE, LH, LL, G>), grid, dim3(Plan<BASE, LH, LL, G>::NT), 0, st, a);
+    hipLaunchKernelGGL((decode_kernel<BASE, LH, LL, G>), grid, dim3(PL::NT), 0, st, d);
     return hipGetLastError() == hipSuccess ? 0 : -5;
   }
 }

@@ -75,6 +75,8 @@ struct DecodeArgs {
   int64_t n_rows[2];       // rows in the high / low pool
   int32_t n_tail;          // fp16 tail rows visible to each layer (taken by the last split)
   int32_t nsplit;          // balanced runs of tiles per unit, one workgroup each
+  int32_t tiles[2];        // tiles of a unit: high pool; both pools
+  int32_t full[2], left[2];// of those: tiles every wave slot holds, and slots that hold one more
   float mu[2][16];         // tq codebooks
 };
 
