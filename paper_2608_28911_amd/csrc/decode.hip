@@ -11,9 +11,16 @@
 // straight into its registers, a record ahead; only a record's metadata goes
 // through LDS.  (With whole records staged in LDS the staging writes, the
 // unaligned segment reads and their bank conflicts were a third of the LDS
-// cycles, 518 a record at batch 16, and LDS was active 61 % of the time: batch
-// 16 at 16384 tokens 47.7 -> 42.6 us a launch, batch 4 at 32768 31.4 -> 29.2,
-// tq at 131072 25.6 -> 24.9.)  Products run on the int8 matrix cores
+// cycles, 518 a record at batch 16, and LDS was active 61 % of the time; now
+// 301 and 42 %.  A segment's registers are loaded again as soon as it is
+// decoded, which keeps a wave's loads spread over its record: all at the
+// record's top, batch 1 at 32768 tokens took 13.8 us a launch instead of 13.2
+// and tq at 131072 25.1 instead of 24.0.  Measured from the staged form: batch
+// 16 at 16384 tokens 48.0 -> 42.6 us a launch, batch 4 at 32768 31.6 -> 28.0,
+// tq at 131072 25.8 -> 24.0, batch 1 at 32768 14.2 -> 13.2.  What is left is
+// mostly the launch's fixed part -- 2.6 us to launch, 2.7 of prologue, 4 of
+// merge -- and memory: at batch 16 the records stream at about 5.6 TB/s.)
+// Products run on the int8 matrix cores
 // (v_mfma_i32_16x16x64_i8), exact in their integer sums.  Per record:
 //   scores  C[16 rows (head, byte) x 16 tokens] += A B: A holds the query of
 //           head h as a fixed-point integer qi = rint(q 2^e) (|qi| < 2^20, e
@@ -654,6 +661,7 @@ struct Plan {
   using GL = Geo<BASE, LL, G>;
   static constexpr int KLD = GH::KLD > GL::KLD ? GH::KLD : GL::KLD, VLD = GH::VLD > GL::VLD ? GH::VLD : GL::VLD;
   static constexpr int NML = GH::NML;
+  static constexpr int MSTAGE = 2 * GH::MB;                 // bytes of a record's metadata
   static constexpr int PV = GH::PV > GL::PV ? GH::PV : GL::PV;
   static constexpr int NGV = GH::NGV;
   static constexpr int NG = GH::NG;
@@ -663,7 +671,7 @@ struct Plan {
   // LDS of a workgroup of nw waves with rh / rl table replicas (the Shared
   // layout below, with margin)
   static constexpr int lds_bytes(int nw, int rh, int rl) {
-    return nw * (NML * 1024 + PV + 2112 + 256) + (Traits<BASE, LH>::LUTDW * rh + Traits<BASE, LL>::LUTDW * rl) * 4 +
+    return nw * (MSTAGE + PV + 256) + (Traits<BASE, LH>::LUTDW * rh + Traits<BASE, LL>::LUTDW * rl) * 4 +
            (GH::NPAIR + GL::NPAIR) * 64 * 16 + 4 * kD * 4 + 2080 + 3104 + 640;
   }
   // 8 waves: 2 per SIMD, one workgroup per compute unit.  A level pair whose
@@ -709,9 +717,8 @@ struct Shared {
   // decode tables (high pool, low pool) first: their offsets fit the 16-bit
   // immediate offset of an LDS read, so a lookup needs no base add
   alignas(16) uint32_t lut[PL::LUTH + PL::LUTL];
-  alignas(16) uint8_t meta[PL::NW][PL::NML * 1024];          // per wave: the record's metadata
-  alignas(16) Fin fin[PL::NW];                               // per wave: its state when its records are done
-  alignas(16) uint8_t pv[PL::NW][PL::PV];                    // per wave int8 weights
+  alignas(16) uint8_t meta[PL::NW][PL::MSTAGE];              // per wave: the record's metadata
+  alignas(16) uint8_t pv[PL::NW][PL::PV];                    // per wave int8 weights, later its Fin
   float qorig[4][kD];                                        // query as given (fp16 tail)
   Fin tfin;                                                  // the fp16 tail's state
   TailScratch ts;
@@ -722,6 +729,12 @@ struct Shared {
   float zc[PL::NW][4][4];                                    // per wave, head, group: sum p * zero
   int last;
 };
+
+template <class PL>
+__device__ inline Fin* wave_fin(Shared<PL>& sm, int w) {
+  static_assert(PL::PV >= int(sizeof(Fin)) && PL::PV % 16 == 0, "state in the weight array");
+  return reinterpret_cast<Fin*>(sm.pv[w]);
+}
 
 template <int NGV>
 struct WaveState {
@@ -765,7 +778,8 @@ __device__ inline float comb3_score(const int4v& c) {
 // bit within (32 lines are a whole number of dwords, so blocks two apart share
 // it).
 struct LaneGeo {
-  int kb[2], vb[2], kstep, vstep, ksh[2], vsh[2];
+  int kb[2], vb[2], kstep, vstep;            // what a load needs
+  int ksh[2], vsh[2];                        // what the extraction needs
 };
 
 // What a lane's geometry needs of the segments of one body, in scalars: bits
@@ -846,32 +860,35 @@ __device__ inline void load_dwords(__amdgpu_buffer_rsrc_t rs, int off, uint32_t*
   }
 }
 
-// Loads a record straight into the registers that use it: each lane the
+// Loads of a record straight into the registers that use it: each lane the
 // dwords of its own segments, through a buffer descriptor bounded by the
 // record's size (what a load reads past its end is 0, without memory traffic).
-// Every record takes the same loads, whichever its pool; with `any` false
-// (no record is left) they are bounded by 0 bytes and read nothing.
+// Every record takes the same loads, whichever its pool; with `any` false (no
+// record is left) they are bounded by 0 bytes and read nothing.
 template <int BASE, int LH, int LL, int G, class PL>
-__device__ inline void load_record(const PoolGeom& g, const uint8_t* unit, int tile, int nt0, bool any, const LaneGeo& lg,
-                                   Record<PL>& r, int lane) {
-  const bool hi = tile < nt0;
-  const uint8_t* rec = hi ? unit + int64_t(tile) * PL::GH::RB : unit + g.lo_offset + int64_t(tile - nt0) * PL::GL::RB;
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(rec), 0, !any ? 0 : hi ? PL::GH::RB : PL::GL::RB, kBufferWord3);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) load_dwords<PL::KLD>(rs, lg.kb[i & 1] + (i >> 1) * lg.kstep, r.k[i]);
-#pragma unroll
-  for (int i = 0; i < PL::NML; ++i) {
-    const uint4v x = __builtin_amdgcn_raw_buffer_load_b128(rs, (hi ? 2 * tile_bytes(LH) : 2 * tile_bytes(LL)) + i * 1024 + lane * 16, 0, 0);
-    r.m[i] = make_uint4(x.x, x.y, x.z, x.w);
+struct RecordSource {
+  __amdgpu_buffer_rsrc_t rs;
+  int meta;
+  __device__ inline RecordSource(const PoolGeom& g, const uint8_t* unit, int tile, int nt0, bool any) {
+    const bool hi = tile < nt0;
+    const uint8_t* rec = hi ? unit + int64_t(tile) * PL::GH::RB : unit + g.lo_offset + int64_t(tile - nt0) * PL::GL::RB;
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(rec), 0, !any ? 0 : hi ? PL::GH::RB : PL::GL::RB, kBufferWord3);
+    meta = hi ? 2 * tile_bytes(LH) : 2 * tile_bytes(LL);
   }
-  int vb[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    vb[i] = i < 2 ? lg.vb[i] : vb[i - 2] + lg.vstep;
-    load_dwords<PL::VLD>(rs, vb[i], r.v[i]);
+  __device__ inline void k(const LaneGeo& lg, int i, Record<PL>& r) const {
+    load_dwords<PL::KLD>(rs, lg.kb[i & 1] + (i >> 1) * lg.kstep, r.k[i]);
   }
-}
+  __device__ inline void m(int lane, Record<PL>& r) const {
+#pragma unroll
+    for (int i = 0; i < PL::NML; ++i) {
+      const uint4v x = __builtin_amdgcn_raw_buffer_load_b128(rs, meta + i * 1024 + lane * 16, 0, 0);
+      r.m[i] = make_uint4(x.x, x.y, x.z, x.w);
+    }
+  }
+  __device__ inline void v(const LaneGeo& lg, int i, Record<PL>& r) const {
+    load_dwords<PL::VLD>(rs, lg.vb[i & 1] + (i >> 1) * lg.vstep, r.v[i]);
+  }
+};
 
 // Per head, of the query x (affine) or the rotated query (bases 1, 2) held by one
 // thread per (head, channel) -- whole waves, 64 channels of one head each:
@@ -1012,8 +1029,9 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
     const uint4 v = sm.aq[A0 + pair][lane];
     return __builtin_bit_cast(int4v, uint4v{v.x, v.y, v.z, v.w});
   };
-  int4v Aq[NG == 1 ? Tr::NCK : 1];
-  if constexpr (NG == 1) {
+  constexpr bool AREG = NG == 1;
+  int4v Aq[AREG ? Tr::NCK : 1];
+  if constexpr (AREG) {
 #pragma unroll
     for (int c = 0; c < Tr::NCK; ++c) Aq[c] = aq(c);
   }
@@ -1032,7 +1050,10 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
   for (int k = 0; k < Tr::NSV; ++k) vmask[k] <<= S;
   // softmax lanes: where token 16 blk + n of each block lands in the weight
   // operands (value group 0, plane 0, row 4r)
-  if (POOL == 1 && i0 > 0) pvwq = *reinterpret_cast<const uint4*>(kPoolConst<BASE, L>.pvw[lane]);
+  if (POOL == 1 && i0 > 0) {
+    geo = lane_geo<BASE, LH, LL>(false, lane);
+    pvwq = *reinterpret_cast<const uint4*>(kPoolConst<BASE, L>.pvw[lane]);
+  }
   const uint32_t pvwr[4] = {pvwq.x, pvwq.y, pvwq.z, pvwq.w};
   // softmax lanes: token n of each 16-token block, head r.  Per query group
   // of head r, times the softmax scale: the sum of q (zero-point term) and
@@ -1053,27 +1074,31 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
 
   for (int it = i0; it < i1; ++it) {
     const int tile = first + stride * it;
-    // this record's segments and metadata out of the load registers, then
-    // the next record's loads into them
-    uint32_t kseg[4][Tr::KSEGW], vseg[8][Tr::VSEGW];
+    // each segment leaves its load registers when it is decoded, and the next
+    // record's load takes them (the empty statements keep the extraction
+    // before the load: sunk below it, it would need registers of its own)
+    const RecordSource<BASE, LH, LL, G, PL> next(a.g, unit, tile + stride, nt0, it + 1 < count);
+    if (POOL == 0 && it + 1 == i1) {         // the next one is the low pool's: its places, this one's bits
+      const int k0 = geo.ksh[0], k1 = geo.ksh[1], v0 = geo.vsh[0], v1 = geo.vsh[1];
+      geo = lane_geo<BASE, LH, LL>(false, lane);
+      geo.ksh[0] = k0, geo.ksh[1] = k1, geo.vsh[0] = v0, geo.vsh[1] = v1;
+    }
+    auto k_segment = [&](int i, uint32_t (&seg)[Tr::KSEGW]) {
+      normalize<Tr::KSEGW, Ge::KLD>(R.k[i], geo.ksh[i & 1], seg);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) normalize<Tr::KSEGW, Ge::KLD>(R.k[i], geo.ksh[i & 1], kseg[i]);
+      for (int k = 0; k < Tr::KSEGW; ++k) __asm__ volatile("" : "+v"(seg[k]));
+      next.k(geo, i, R);
+    };
+    auto v_segment = [&](int i, uint32_t (&seg)[Tr::VSEGW]) {
+      normalize<Tr::VSEGW, Ge::VLD>(R.v[i], geo.vsh[i & 1], seg);
 #pragma unroll
-    for (int i = 0; i < PL::NML; ++i) *reinterpret_cast<uint4*>(kmeta + i * 1024 + lane * 16) = R.m[i];
+      for (int k = 0; k < Tr::VSEGW; ++k) __asm__ volatile("" : "+v"(seg[k]));
+      next.v(geo, i, R);
+    };
 #pragma unroll
-    for (int i = 0; i < 8; ++i) normalize<Tr::VSEGW, Ge::VLD>(R.v[i], geo.vsh[i & 1], vseg[i]);
-    // (the empty statements keep the extraction here: sunk below the loads,
-    // it would need a second set of load registers)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int k = 0; k < Tr::KSEGW; ++k) __asm__ volatile("" : "+v"(kseg[i][k]));
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int k = 0; k < Tr::VSEGW; ++k) __asm__ volatile("" : "+v"(vseg[i][k]));
-    if (POOL == 0 && it + 1 == i1) geo = lane_geo<BASE, LH, LL>(false, lane);     // the next one is the low pool's
-    load_record<BASE, LH, LL, G>(a.g, unit, tile + stride, nt0, it + 1 < count, geo, R, lane);
+    for (int i = 0; i < PL::NML; ++i)
+      if (PL::MSTAGE % 1024 == 0 || lane * 16 < PL::MSTAGE) *reinterpret_cast<uint4*>(kmeta + i * 1024 + lane * 16) = R.m[i];
+    next.m(lane, R);
     if (it == 0) SEMKV_STAMP_FINE(16);
     const int ptile = POOL ? tile - nt0 : tile;
     const int nvalid = nrows - int64_t(ptile) * kSlots < kSlots ? int(nrows - int64_t(ptile) * kSlots) : kSlots;
@@ -1128,13 +1153,23 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
     // software pipeline: the next block's table reads are in flight during
     // the current block's products
     int4v Bk[2][Tr::NCK];
-    chunk_operands<BASE, L, S, KFULL, Tr::KSEGW, Tr::NSK, Tr::NCK>(kseg[0], kmask, lut, Bk[0]);
+    auto k_operands = [&](int i, int4v (&B)[Tr::NCK]) {
+      uint32_t seg[Tr::KSEGW];
+      k_segment(i, seg);
+      chunk_operands<BASE, L, S, KFULL, Tr::KSEGW, Tr::NSK, Tr::NCK>(seg, kmask, lut, B);
+    };
+    auto v_operands = [&](int i, int4v (&B)[Tr::NCV]) {
+      uint32_t seg[Tr::VSEGW];
+      v_segment(i, seg);
+      chunk_operands<BASE, L, S, VFULL, Tr::VSEGW, Tr::NSV, Tr::NCV>(seg, vmask, lut, B);
+    };
+    k_operands(0, Bk[0]);
     constexpr bool DEFER = NG == 1;          // score arithmetic after the value segment reads
     int4v acck[DEFER ? 4 : 1][NG];
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
       if constexpr (NVM > 1) load_km(blk);
-      if (blk + 1 < 4) chunk_operands<BASE, L, S, KFULL, Tr::KSEGW, Tr::NSK, Tr::NCK>(kseg[blk + 1], kmask, lut, Bk[(blk + 1) & 1]);
+      if (blk + 1 < 4) k_operands(blk + 1, Bk[(blk + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
       int4v acc[NG];
       static_for<NG>([&](auto I) {
@@ -1145,7 +1180,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
           if constexpr (Ge::pair_used(i, ch)) {              // else chunk ch holds no channel of group i
             int4v A;
             constexpr int pair = Ge::pair_of(i, ch);
-            if constexpr (NG == 1) A = Aq[ch];
+            if constexpr (AREG) A = Aq[ch];
             else A = aq(pair);
             acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, Bk[blk & 1][ch], acc[i], 0, 0, 0);
           }
@@ -1163,7 +1198,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
     // trip overlaps it
     if constexpr (NVM > 1) load_vm();
     int4v Bv[2][Tr::NCV];
-    chunk_operands<BASE, L, S, VFULL, Tr::VSEGW, Tr::NSV, Tr::NCV>(vseg[0], vmask, lut, Bv[0]);
+    v_operands(0, Bv[0]);
     if constexpr (DEFER) {
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) lg[blk] = score(blk, acck[blk]);
@@ -1270,7 +1305,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
           Aw[c] = __builtin_bit_cast(int4v, uint4v{v.x, v.y, v.z, v.w});
         }
       }
-      if (cb + 1 < 8) chunk_operands<BASE, L, S, VFULL, Tr::VSEGW, Tr::NSV, Tr::NCV>(vseg[cb + 1], vmask, lut, Bv[(cb + 1) & 1]);
+      if (cb + 1 < 8) v_operands(cb + 1, Bv[(cb + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int c = 0; c < Tr::NCV; ++c) st.cv[cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(Aw[c], Bv[cb & 1][c], st.cv[cb], 0, 0, 0);
@@ -1300,7 +1335,7 @@ __device__ void wave_finish(Shared<PL>& sm, WaveState<PL::NGV>& st) {
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  Fin* f = &sm.fin[wave];
+  Fin* f = wave_fin(sm, wave);
   if (n == 0) {
     f->m[r] = st.m;
     f->l[r] = st.l;
@@ -1352,13 +1387,13 @@ __device__ inline float fwht_rows(float x, float (*xch)[kD]) {
 
 // fp16 tail of generated tokens (1 to 64 rows): its attention state goes to
 // sm.tfin.  Runs after the workgroup's records, when the decode tables and the
-// weight arrays are free: the K tail is staged in the table area and the V
-// tail in the weight area (both in one round trip), then every thread works:
+// query operands are free: the K and V tails are staged in the table area
+// (both in one round trip), then every thread works:
 // 8 threads per row for the scores, one wave per head for the softmax, one
 // thread per (head, channel) for the values.
 template <int BASE, class PL>
 __device__ void tail_split(const DecodeArgs& a, Shared<PL>& sm, int b, int layer, int kvh) {
-  static_assert(sizeof(sm.lut) >= kSlots * kD * 2 && sizeof(sm.pv) >= kSlots * kD * 2, "tail staging");
+  static_assert(sizeof(sm.lut) >= 2 * kSlots * kD * 2, "tail staging");
   static_assert(PL::NT == 4 * kD, "one thread per (head, channel)");
   const PoolGeom& g = a.g;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1367,7 +1402,7 @@ __device__ void tail_split(const DecodeArgs& a, Shared<PL>& sm, int b, int layer
   const uint16_t* kt = a.tail + ((((int64_t(b) * g.n_layers + layer) * g.n_kv_heads + kvh) * 2) * kSlots) * kD;
   const uint16_t* vt = kt + kSlots * kD;
   uint4* kl = reinterpret_cast<uint4*>(sm.lut);             // [64 rows][16 pieces of 8 fp16]
-  uint4* vl = reinterpret_cast<uint4*>(&sm.pv[0][0]);
+  uint4* vl = kl + kSlots * kD / 8;
   {
     // piece i (8 channels of row i / 16); the two pieces of a thread: i0, i1
     const int i0 = tid, i1 = tid + PL::NT;
@@ -1519,8 +1554,8 @@ __device__ void merge_splits(const DecodeArgs& a, Shared<PL>& sm, int vb, int la
     M = Mn;
   }
   struct Quarters { float m[4][4], l[4][4]; float4v o[4][4][32]; };
-  static_assert(sizeof(Quarters) <= sizeof(sm.fin), "merge scratch");
-  Quarters& qs = *reinterpret_cast<Quarters*>(&sm.fin[0]);
+  static_assert(sizeof(Quarters) <= sizeof(sm.pv), "merge scratch");
+  Quarters& qs = *reinterpret_cast<Quarters*>(&sm.pv[0][0]);
   if (mine) {
     if (cq == 0) {
       qs.m[h][q] = M;
@@ -1611,7 +1646,14 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   LaneGeo geo = {};
   if (count > 0) geo = lane_geo<BASE, LH, LL>(tile0 < nt0, lane);
   Record<PL> R;
-  load_record<BASE, LH, LL, G>(g, unit, tile0, nt0, count > 0, geo, R, lane);
+  {
+    const RecordSource<BASE, LH, LL, G, PL> rec(g, unit, tile0, nt0, count > 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rec.k(geo, i, R);
+    rec.m(lane, R);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) rec.v(geo, i, R);
+  }
 
   {
     uint4* d = reinterpret_cast<uint4*>(sm.lut);
@@ -1673,12 +1715,12 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   if (qt) {
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, sm.fin[w].m[h]);
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, wave_fin(sm, w)->m[h]);
     if (tail) M = fmaxf(M, sm.tfin.m[h]);
     float Lsum = 0.0f, o = 0.0f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const Fin* f = &sm.fin[w];
+      const Fin* f = wave_fin(sm, w);
       const float sc = f->m[h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(f->m[h] - M);
       Lsum += f->l[h] * sc;
       o += f->o[h][c] * sc;
