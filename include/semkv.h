@@ -102,7 +102,7 @@ typedef struct semkv_config {
  *  flags:  uint32 [batch][flag_words]: bit i%32 of word i/32 is 1 iff token i
  *          has the high precision (the 1-bit per-token flag of Sec. 4.1);
  *          then (from word batch*flag_words rounded up to a multiple of 64)
- *          the ranker's scratch for prompts longer than 4096 tokens, per
+ *          the ranker's scratch for prompts longer than 16384 tokens, per
  *          sequence three histograms of 2048, 2048 and 1024 words, which are
  *          zero again when each semkv_rank call ends, 16 words of selection
  *          state and two counts per 4096-token chunk.  flag_bytes covers both.
@@ -162,7 +162,7 @@ int semkv_rank_sizes(const semkv_cache* c, int64_t T, int64_t* n_hi, int64_t* n_
  * bits of tokens [0, T) and the slot lists hi_idx: device int32
  * [batch][K] (ascending), lo_idx: device int32 [batch][T-K] (ascending); a
  * list with no entries may be NULL.
- * A NaN score sets SEMKV_STATUS_NAN_SCORE.  Prompts of up to 4096 tokens take
+ * A NaN score sets SEMKV_STATUS_NAN_SCORE.  Prompts of up to 16384 tokens take
  * one launch (one workgroup per sequence); longer ones take five, one
  * workgroup per 4096-token chunk, with the scratch at the end of `flags`.
  * Calls that overlap on one cache race. */

@@ -1,20 +1,22 @@
 // rank.hip -- exact top-K importance ranking (Eq. 4-5) for gfx950.
 //
-// One 1024-thread workgroup per sequence.  Scores become order-preserving
-// 32-bit keys (-0 taken as +0); a 4-pass 8-bit radix select finds the K-th
-// largest key theta and how many of the keys equal to it are taken (equal
-// keys are taken by increasing token index).  Importance scores are heavily
-// tied (integer Zipf draws, peaked accumulated-attention weights), so the
-// histogram passes put most keys of a wave in one bin: each wave keeps its
-// own histogram and adds its most common bin with a single atomic.  The keys
-// of the bin the first pass picks are gathered into LDS when they fit, and
-// the remaining passes count only them.  The flag and compaction pass then stages the keys through LDS in segments,
-// loaded coalesced, so that each thread owns a contiguous run of 16 tokens:
-// block-wide prefix counts give every token its tie rank and its slot in the
-// ascending high and low slot lists.
+// Sequences of up to kRankWG = 16384 tokens take one launch, a 1024-thread
+// workgroup per sequence that reads each score once and keeps it in a register
+// as an order-preserving 32-bit key (-0 taken as +0); thread t of pass-round j
+// holds token 1024 j + t.  A 4-pass 8-bit radix select finds the K-th largest
+// key theta and how many of the keys equal to it are taken (equal keys are
+// taken by increasing token index).  Importance scores are heavily tied
+// (integer Zipf draws, peaked accumulated-attention weights), so a wave adds
+// the bin of its first counted key with a single atomic.  Every pass has a
+// histogram of its own and every wave selects the bin itself, so a pass costs
+// one barrier.  Ballots then give each wave's keys above and equal to theta;
+// one scan over the (round, wave) counts, and a lane's count of the lower
+// lanes, give every token its slot: a token's place in the high list is the
+// keys above theta before it and the taken ones equal to theta before it.
+// Bound by latency (barriers, LDS atomics), not by the 8 bytes a token.
 //
-// Sequences longer than one chunk of kRankChunk = 4096 tokens are ranked by
-// one 256-thread workgroup per chunk instead, in five launches over the same
+// Longer sequences are ranked by one 256-thread workgroup per chunk of
+// kRankChunk = 4096 tokens instead, in five launches over the same
 // grid (chunk, sequence), so that a chunk's scores stay in one L2:
 //   1. histogram of key bits [21, 32) of every token;
 //   2. the bin b1 holding the K-th largest key, then the histogram of bits
@@ -30,6 +32,8 @@
 // the same call clears it again (3 clears the first, 4 the second, 5 the
 // third).  Every workgroup of a launch selects the bin itself from the whole
 // histogram; chunk 0 also records it for the next launch.
+#include <type_traits>
+
 #include "semkv_internal.h"
 
 namespace semkv {
@@ -37,215 +41,154 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRun = 16;                     // tokens per thread in a segment
-constexpr int kSeg = kThreads * kRun;        // tokens per LDS segment
-constexpr int kBatch = 8;                    // score loads in flight per thread
 
 __device__ inline uint32_t order_key(float v) {
   uint32_t u = __float_as_uint(v == 0.0f ? 0.0f : v);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// exclusive prefix sum over the workgroup of one value per thread; returns
-// this thread's prefix and the total
-__device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d);
-    if (lane >= d) x += y;
-  }
-  if (lane == 63) wsum[wave] = x;
-  __syncthreads();
-  if (wave == 0) {
-    uint32_t w = lane < kWaves ? wsum[lane] : 0u, s = w;
-#pragma unroll
-    for (int d = 1; d < kWaves; d <<= 1) {
-      const uint32_t y = __shfl_up(s, d);
-      if (lane >= d) s += y;
-    }
-    if (lane < kWaves) wsum[lane] = s - w;
-    if (lane == kWaves - 1) wsum[kWaves] = s;
-  }
-  __syncthreads();
-  const uint32_t r = wsum[wave] + x - v;
-  *total = wsum[kWaves];
-  __syncthreads();
-  return r;
+// inclusive prefix sum over the 64 lanes of a wave (whole wave active): rows
+// of 16 by row shifts, then the row totals by row broadcasts
+__device__ inline uint32_t wave_scan(uint32_t x) {
+  auto step = [](uint32_t v, auto ctrl, auto rows) {
+    return v + uint32_t(__builtin_amdgcn_update_dpp(0, int(v), decltype(ctrl)::value, decltype(rows)::value, 0xF, false));
+  };
+  x = step(x, std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});   // row_shr 1, 2, 4, 8
+  x = step(x, std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+  x = step(x, std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+  x = step(x, std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+  x = step(x, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});   // row_bcast 15, 31
+  return step(x, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
 }
 
-__global__ __launch_bounds__(kThreads) void rank_kernel(RankArgs a) {
-  __shared__ uint32_t hist[kWaves][256];
-  __shared__ alignas(16) uint32_t keys[kSeg];
-  __shared__ uint32_t wsum[kWaves + 1];
-  __shared__ uint32_t s_prefix;
-  __shared__ int64_t s_krem;
-  __shared__ uint32_t s_cand, s_ncand;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float* s = a.scores + int64_t(b) * a.ld_s;
-  const int64_t T = a.T, K = a.K;
+// add the counted keys' bins to an LDS histogram: a wave's most common case
+// (its first counted key's bin) in one atomic, the others singly
+__device__ inline void hist_add(uint32_t* hist, uint32_t bin, bool in) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t act = __ballot(in);
+  if (act != 0) {
+    const int lead = __builtin_ctzll(act);
+    const uint32_t b0 = __shfl(bin, lead);
+    const uint64_t same = __ballot(in && bin == b0);
+    if (lane == lead) atomicAdd(&hist[b0], uint32_t(__popcll(same)));
+    if (in && bin != b0) atomicAdd(&hist[bin], 1u);
+  }
+}
 
-  // ---- radix select of the K-th largest key, 8 bits per pass.  After the
-  // first pass only the keys of the chosen bin can still decide theta: when
-  // they fit the LDS key buffer they are gathered there once, and the later
-  // passes count them alone instead of reading every score again.
-  bool nan_seen = false;
-  uint32_t prefix = 0, pmask = 0;
-  int64_t krem = K;
+// one workgroup per sequence of up to 1024 R tokens, R keys per thread
+template <int R>
+__global__ __launch_bounds__(kThreads) void rank_kernel(RankArgs a) {
+  constexpr int NE = R * kWaves, PER = (NE + 63) / 64;       // (round, wave) counts, and of them per lane of the scan
+  __shared__ alignas(16) uint32_t hist[4][256];
+  __shared__ uint32_t cnt[PER * 64];                         // keys above theta << 16 | keys equal to it
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int T = int(a.T);
+  const uint32_t K = uint32_t(a.K);
+  // reads past the sequence's T scores return 0 and are not counted
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.scores + int64_t(b) * a.ld_s), 0, T * 4, kBufferWord3);
+  uint32_t key[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) key[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (j * kThreads + tid) * 4, 0, 0);
+  (&hist[0][0])[tid] = 0u;
+  bool nan = false;
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const float v = __uint_as_float(key[j]);
+    nan |= j * kThreads + tid < T && isnan(v);
+    key[j] = order_key(v);
+  }
+  __syncthreads();
+
+  // ---- radix select of the K-th largest key, 8 bits per pass
+  uint32_t theta = 0, krem = K;
   if (K > 0) {
-    bool staged = false;                     // candidates in keys[0, ncand)
-    uint32_t ncand = 0;
+#pragma unroll
     for (int d = 3; d >= 0; --d) {
-      for (int i = tid; i < kWaves * 256; i += kThreads) (&hist[0][0])[i] = 0u;
+      uint32_t* H = hist[3 - d];
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (j * kThreads + wave * 64 < T)                    // the same for the whole wave
+          hist_add(H, (key[j] >> (8 * d)) & 255u,
+                   j * kThreads + tid < T && (d == 3 || (key[j] >> (8 * d + 8)) == (theta >> (8 * d + 8))));
       __syncthreads();
-      // add key k (counted when `in`) to this wave's histogram of digit d
-      auto count = [&](uint32_t k, bool in) {
-        const uint32_t bin = (k >> (8 * d)) & 255u;
-        const uint64_t act = __ballot(in);
-        if (act != 0) {
-          // the wave's first counted key's bin in one atomic, the rest singly
-          const int lead = __builtin_ctzll(act);
-          const uint32_t b0 = __shfl(bin, lead);
-          const uint64_t same = __ballot(in && bin == b0);
-          if (lane == lead) atomicAdd(&hist[wave][b0], uint32_t(__popcll(same)));
-          if (in && bin != b0) atomicAdd(&hist[wave][bin], 1u);
+      // lane l takes bins 255 - 4 l .. 252 - 4 l (descending key order)
+      const uint4 q = *reinterpret_cast<const uint4*>(H + 252 - 4 * lane);
+      const uint32_t c[4] = {q.w, q.z, q.y, q.x}, sum = q.x + q.y + q.z + q.w;
+      uint32_t above = wave_scan(sum) - sum;                 // keys in the bins of lower lanes
+      const uint64_t has = __ballot(above < krem && above + sum >= krem);
+      const int src = has ? __builtin_ctzll(has) : 0;
+      uint32_t bin = 0, left = krem;
+      bool found = false;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (!found && above + c[i] >= krem) {
+          bin = uint32_t(255 - 4 * lane - i);
+          left = krem - above;
+          found = true;
         }
-      };
-      if (!staged) {
-        for (int64_t i0 = 0; i0 < T; i0 += kBatch * kThreads) {
-          float v[kBatch];                   // all loads of the batch in flight at once
-#pragma unroll
-          for (int j = 0; j < kBatch; ++j) {
-            const int64_t i = i0 + j * kThreads + tid;
-            v[j] = i < T ? s[i] : 0.0f;
-          }
-#pragma unroll
-          for (int j = 0; j < kBatch; ++j) {
-            const int64_t i = i0 + j * kThreads + tid;
-            nan_seen |= i < T && isnan(v[j]);
-            const uint32_t k = order_key(v[j]);
-            count(k, i < T && (k & pmask) == prefix);
-          }
-        }
-      } else {
-        for (uint32_t i0 = 0; i0 < ncand; i0 += kThreads) {
-          const uint32_t i = i0 + tid;
-          const uint32_t k = i < ncand ? keys[i] : 0u;
-          count(k, i < ncand && (k & pmask) == prefix);
-        }
+        above += c[i];
       }
-      __syncthreads();
-      // bin counts over the waves, then the bin holding the krem-th largest
-      // key: thread t < 256 takes bin 255 - t (descending key order)
-      uint32_t cnt = 0;
-      if (tid < 256) {
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) cnt += hist[w][255 - tid];
-      }
-      uint32_t total;
-      const uint32_t above = block_exclusive_scan(cnt, wsum, &total);   // keys in higher bins
-      if (tid < 256 && int64_t(above) < krem && int64_t(above) + cnt >= krem) {
-        s_prefix = prefix | (uint32_t(255 - tid) << (8 * d));
-        s_krem = krem - above;
-        s_cand = cnt;
-      }
-      __syncthreads();
-      prefix = s_prefix;
-      krem = s_krem;
-      pmask |= 255u << (8 * d);
-      if (d > 0 && !staged && s_cand <= uint32_t(kSeg)) {
-        // gather the chosen bin's keys (exactly s_cand of them) into LDS
-        if (tid == 0) s_ncand = 0u;
-        __syncthreads();
-        for (int64_t i0 = 0; i0 < T; i0 += kBatch * kThreads) {
-          float v[kBatch];
-#pragma unroll
-          for (int j = 0; j < kBatch; ++j) {
-            const int64_t i = i0 + j * kThreads + tid;
-            v[j] = i < T ? s[i] : 0.0f;
-          }
-#pragma unroll
-          for (int j = 0; j < kBatch; ++j) {
-            const int64_t i = i0 + j * kThreads + tid;
-            const uint32_t k = order_key(v[j]);
-            const bool in = i < T && (k & pmask) == prefix;
-            const uint64_t act = __ballot(in);
-            if (act != 0) {
-              const int lead = __builtin_ctzll(act);
-              uint32_t base = 0u;
-              if (lane == lead) base = atomicAdd(&s_ncand, uint32_t(__popcll(act)));
-              base = __shfl(base, lead);
-              if (in) keys[base + uint32_t(__popcll(act & ((uint64_t(1) << lane) - 1u)))] = k;
-            }
-          }
-        }
-        __syncthreads();
-        ncand = s_ncand;
-        staged = true;
-      }
-      __syncthreads();
+      theta |= uint32_t(__builtin_amdgcn_readlane(int(bin), src)) << (8 * d);
+      krem = uint32_t(__builtin_amdgcn_readlane(int(left), src));
     }
   }
-  if (nan_seen) atomicOr(a.status, 1);
+  if (nan) atomicOr(a.status, 1);
   // keys above theta are taken, and the first `ties` keys equal to it
-  const uint32_t theta = prefix;
-  const uint32_t ties = K > 0 ? uint32_t(krem) : 0u;
+  const uint32_t ties = K > 0 ? krem : 0u;
 
-  // ---- flags and ascending slot lists, one LDS segment of kSeg keys at a time
-  int32_t* hi_out = a.hi_idx + int64_t(b) * K;
-  int32_t* lo_out = a.lo_idx + int64_t(b) * (T - K);
-  uint32_t run_tie = 0, run_hi = 0;          // before this segment (T < 2^29)
-  for (int64_t seg0 = 0; seg0 < T; seg0 += kSeg) {
-    const int n = T - seg0 < kSeg ? int(T - seg0) : kSeg;
+  // ---- each (round, wave)'s keys above and equal to theta, and those before it
 #pragma unroll
-    for (int j = 0; j < kRun; ++j) {
-      const int i = j * kThreads + tid;
-      if (i < n) keys[i] = order_key(s[seg0 + i]);
-    }
-    __syncthreads();
-    // this thread's run of 16 keys, in registers (keys past n are not used)
-    const int r0 = tid * kRun, nr = n - r0 < 0 ? 0 : (n - r0 < kRun ? n - r0 : kRun);
-    uint32_t kr[kRun];
+  for (int j = 0; j < R; ++j) {
+    const bool in = j * kThreads + tid < T && K > 0;
+    const uint64_t gt = __ballot(in && key[j] > theta), eq = __ballot(in && key[j] == theta);
+    if (lane == 0) cnt[j * kWaves + wave] = (uint32_t(__popcll(gt)) << 16) | uint32_t(__popcll(eq));
+  }
+  __syncthreads();
+  if (wave == 0) {
+    uint32_t c[PER], sum = 0;
 #pragma unroll
-    for (int j = 0; j < kRun / 4; ++j) {
-      const uint4 q = reinterpret_cast<const uint4*>(keys + r0)[j];
-      kr[4 * j] = q.x;
-      kr[4 * j + 1] = q.y;
-      kr[4 * j + 2] = q.z;
-      kr[4 * j + 3] = q.w;
+    for (int i = 0; i < PER; ++i) {
+      c[i] = lane * PER + i < NE ? cnt[lane * PER + i] : 0u;
+      sum += c[i];
     }
-    uint32_t nt = 0;
+    uint32_t before = wave_scan(sum) - sum;
 #pragma unroll
-    for (int j = 0; j < kRun; ++j) nt += (j < nr && kr[j] == theta) ? 1u : 0u;
-    uint32_t tot_tie;
-    uint32_t tr = run_tie + block_exclusive_scan(nt, wsum, &tot_tie);   // tie rank of the run's first tie
-    uint32_t bits = 0, nf = 0;
+    for (int i = 0; i < PER; ++i) {
+      cnt[lane * PER + i] = before;
+      before += c[i];
+    }
+  }
+  __syncthreads();
+
+  // ---- flags and ascending slot lists
+  int32_t* hi_out = a.hi_idx + int64_t(b) * a.K;
+  int32_t* lo_out = a.lo_idx + int64_t(b) * (a.T - a.K);
+  const uint64_t below = (uint64_t(1) << lane) - 1u;
 #pragma unroll
-    for (int j = 0; j < kRun; ++j) {
-      const uint32_t k = kr[j];
-      const bool f = j < nr && K > 0 && (k > theta || (k == theta && tr < ties));
-      tr += (j < nr && k == theta) ? 1u : 0u;
-      bits |= f ? 1u << j : 0u;
-      nf += f ? 1u : 0u;
-    }
-    // a flag word is the runs of two neighbouring lanes (kRun = 16)
-    const uint32_t other = __shfl_xor(bits, 1);
-    if ((tid & 1) == 0 && nr > 0) a.flags[int64_t(b) * a.flag_words + ((seg0 + r0) >> 5)] = bits | (other << 16);
-    uint32_t tot_hi;
-    uint32_t hb = run_hi + block_exclusive_scan(nf, wsum, &tot_hi);
-    uint32_t lb = uint32_t(seg0 + r0) - hb;
-    for (int j = 0; j < nr; ++j) {
-      if ((bits >> j) & 1u) hi_out[hb++] = int32_t(seg0 + r0 + j);
-      else lo_out[lb++] = int32_t(seg0 + r0 + j);
-    }
-    run_tie += tot_tie;
-    run_hi += tot_hi;
-    __syncthreads();
+  for (int j = 0; j < R; ++j) {
+    const int t0 = j * kThreads + wave * 64, i = t0 + lane;
+    if (t0 >= T) continue;                                   // the same for the whole wave
+    const bool in = i < T && K > 0;
+    const uint64_t gt = __ballot(in && key[j] > theta), eq = __ballot(in && key[j] == theta);
+    const uint32_t pre = cnt[j * kWaves + wave];
+    const uint32_t gb = (pre >> 16) + uint32_t(__popcll(gt & below)), eb = (pre & 0xFFFFu) + uint32_t(__popcll(eq & below));
+    const bool f = in && (key[j] > theta || (key[j] == theta && eb < ties));
+    const uint64_t fl = __ballot(f);
+    if (lane < 2 && t0 + 32 * lane < T) a.flags[int64_t(b) * a.flag_words + (t0 >> 5) + lane] = uint32_t(fl >> (32 * lane));
+    const int hb = int(gb + (eb < ties ? eb : ties));
+    if (f) hi_out[hb] = i;
+    else if (i < T) lo_out[i - hb] = i;
   }
 }
 
 // ------------------------------------------- one workgroup per chunk ----
+
+// Longest sequence of the one-workgroup kernel.  Back to back, microseconds a
+// call, one workgroup / one per chunk: 9.0 / 22 at 4096 tokens, 10.6 / 23 at
+// 8192, 14 / 23 at 10007, 18-20 / 24 at 16384, 29-33 / 24 at 24576.  (The
+// kernel before it, which read the scores again in each pass: 15.8 at 4096.)
+constexpr int64_t kRankWG = 16 * kThreads;
 
 constexpr int kMT = 256;                     // threads of a chunk's workgroup
 constexpr int kMW = kMT / 64;
@@ -342,20 +285,6 @@ __device__ void select_bin(const uint32_t (&c)[NB / kMT], uint32_t krem, uint32_
 __device__ inline void clear_slice(uint32_t* H, int n, int c, int nchunk) {
   const int per = (n + nchunk - 1) / nchunk;
   for (int i = c * per + int(threadIdx.x); i < (c + 1) * per && i < n; i += kMT) H[i] = 0u;
-}
-
-// add the counted keys' bins to an LDS histogram: a wave's most common case
-// (its first counted key's bin) in one atomic, the others singly
-__device__ inline void hist_add(uint32_t* hist, uint32_t bin, bool in) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t act = __ballot(in);
-  if (act != 0) {
-    const int lead = __builtin_ctzll(act);
-    const uint32_t b0 = __shfl(bin, lead);
-    const uint64_t same = __ballot(in && bin == b0);
-    if (lane == lead) atomicAdd(&hist[b0], uint32_t(__popcll(same)));
-    if (in && bin != b0) atomicAdd(&hist[bin], 1u);
-  }
 }
 
 // launches 1-3: PASS 1 counts bits [21, 32) of every key, PASS 2 bits
@@ -506,8 +435,11 @@ __global__ __launch_bounds__(kMT) void rank_final_kernel(RankArgs a) {
 }  // namespace
 
 int launch_rank(const RankArgs& a, int batch, hipStream_t s) {
-  if (a.T <= kRankChunk) {
-    hipLaunchKernelGGL(rank_kernel, dim3(batch), dim3(kThreads), 0, s, a);
+  if (a.T <= kRankWG) {
+    const dim3 grid(unsigned(batch), 1, 1), block(kThreads);
+    if (a.T <= 4 * kThreads) hipLaunchKernelGGL(rank_kernel<4>, grid, block, 0, s, a);
+    else if (a.T <= 8 * kThreads) hipLaunchKernelGGL(rank_kernel<8>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(rank_kernel<16>, grid, block, 0, s, a);
     return hipGetLastError() == hipSuccess ? 0 : -5;
   }
   const dim3 grid(unsigned(rank_chunks(a.T)), unsigned(batch));

@@ -152,6 +152,36 @@ def test_multi_chunk_ranker(r):
         assert not words[off + b * stride:off + b * stride + 5120].any(), "histograms of seq %d not cleared" % b
 
 
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 1023, 1025, 4096, 4097, 8192, 8193, 16383, 16384, 16385, 20481])
+def test_ranker_at_the_edges_of_its_kernels(T):
+    """Around whole waves, rounds of 1024 tokens, the sizes where the number
+    of rounds changes and the one-workgroup kernel's longest sequence: flags
+    and slot lists bit-exact, no tokens, a mix, all but one and all high."""
+    import torch
+    s = _multi_chunk_scores(T, 7) if T >= 64 else np.random.default_rng(T).integers(-3, 3, (3, T)).astype(np.float32)
+    for r in ((0, 1), (26, 100), (T - 1, T), (1, 1)):
+        cfgw = get_config(0, batch=3, n_kv_heads=1, n_q_heads=4, n_layers=1, r_num=r[0], r_den=r[1])
+        cache = U.make_cache(cfgw, T, n_layers=1, max_new=0)
+        hi, lo = cache.rank(torch.from_numpy(s).cuda())
+        hi, lo = hi.cpu().numpy(), lo.cpu().numpy()
+        for b in range(3):
+            f, ohi, olo = O.rank(s[b], r[0], r[1])
+            assert np.array_equal(hi[b], ohi) and np.array_equal(lo[b], olo), "slot lists, r %s seq %d" % (r, b)
+            assert np.array_equal(U.flags_bits(cache, b, T), f), "flags, r %s seq %d" % (r, b)
+        assert cache.status() == 0
+
+
+def test_one_workgroup_ranker_reports_nan():
+    import torch
+    cfgw = get_config(0, batch=2, n_kv_heads=1, n_q_heads=4, n_layers=1)
+    cache = U.make_cache(cfgw, 5000, n_layers=1, max_new=0)
+    s = np.random.default_rng(5).standard_normal((2, 5000)).astype(np.float32)
+    s[1, 4999] = np.nan
+    cache.rank(torch.from_numpy(s).cuda())
+    torch.cuda.synchronize()
+    assert cache.status() & 1
+
+
 def test_multi_chunk_ranker_reports_nan():
     import torch
     cfgw = get_config(0, batch=1, n_kv_heads=1, n_q_heads=4, n_layers=1)
