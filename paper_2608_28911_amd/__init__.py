@@ -18,13 +18,23 @@ INDICATORS = {"delta_norm": _abi.IND_DELTA_NORM, "norm": _abi.IND_NORM, "varianc
               "cosine_delta": _abi.IND_COSINE_DELTA}
 
 
+_raw_stream = None
+
+
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current HIP stream of the current device, as an integer.  Read
+    without building a torch Stream object, which costs a microsecond of the
+    eight that a call took (a short decode launch runs for about as long)."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _raw_stream = (lambda: raw(torch.cuda.current_device())) if raw else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def make_config(n_layers, n_kv_heads, batch, base, L_hi, L_lo, group, r_num, r_den,
@@ -88,12 +98,15 @@ class SemKVCache:
                                      _ptr(self.signs) if self.signs is not None else None,
                                      _ptr(self.status_word)), "semkv_cache_init")
         self._ws = None
+        self._cref = ctypes.byref(self.c)
+        self._lib = lib()
+        self._ratio = (self.c.cfg.r_num, self.c.cfg.r_den, self.c.cfg.max_prompt)
 
     # -- the hot path ------------------------------------------------------
     def rank_sizes(self, T):
         """(n_hi, n_lo): the slot-list lengths semkv_rank writes for T tokens."""
         n_hi, n_lo = ctypes.c_int64(), ctypes.c_int64()
-        check(lib().semkv_rank_sizes(ctypes.byref(self.c), T, ctypes.byref(n_hi), ctypes.byref(n_lo)),
+        check(self._lib.semkv_rank_sizes(self._cref, T, ctypes.byref(n_hi), ctypes.byref(n_lo)),
               "semkv_rank_sizes")
         return n_hi.value, n_lo.value
 
@@ -103,7 +116,12 @@ class SemKVCache:
         import torch
         scores = scores.contiguous()
         B, T = scores.shape
-        n_hi, n_lo = self.rank_sizes(T)
+        rn, rd, most = self._ratio
+        if 1 <= T <= most:                   # as rank_sizes, without a call into the library
+            n_hi = rn * T // rd
+            n_lo = T - n_hi
+        else:
+            n_hi, n_lo = self.rank_sizes(T)  # raises
         if out is None:
             hi = torch.empty((B, n_hi), dtype=torch.int32, device=scores.device)
             lo = torch.empty((B, n_lo), dtype=torch.int32, device=scores.device)
@@ -111,7 +129,7 @@ class SemKVCache:
             hi, lo = out
             assert hi.shape == (B, n_hi) and lo.shape == (B, n_lo) and hi.dtype == lo.dtype == torch.int32
             assert hi.is_contiguous() and lo.is_contiguous()
-        check(lib().semkv_rank(ctypes.byref(self.c), _ptr(scores), T, _ptr(hi), _ptr(lo), _stream()),
+        check(self._lib.semkv_rank(self._cref, _ptr(scores), T, _ptr(hi), _ptr(lo), _stream()),
               "semkv_rank")
         return hi, lo
 
@@ -124,7 +142,7 @@ class SemKVCache:
         else:
             sL, (sB, sH, sT) = 0, st[:3]
         T = K.shape[-2]
-        check(lib().semkv_quantize_pack(ctypes.byref(self.c), layer, _ptr(K), _ptr(V), sL, sB, sH, sT, T,
+        check(self._lib.semkv_quantize_pack(self._cref, layer, _ptr(K), _ptr(V), sL, sB, sH, sT, T,
                                         _ptr(hi_idx), _ptr(lo_idx), _stream()), "semkv_quantize_pack")
 
     def dequant(self, layer):
@@ -137,7 +155,7 @@ class SemKVCache:
         v = torch.empty_like(k)
         if n == 0:
             return k, v
-        check(lib().semkv_dequant(ctypes.byref(self.c), layer, _ptr(k), _ptr(v), _stream()), "semkv_dequant")
+        check(self._lib.semkv_dequant(self._cref, layer, _ptr(k), _ptr(v), _stream()), "semkv_dequant")
         return k, v
 
     def score_kv_norm(self, X, scores=None):
@@ -149,28 +167,28 @@ class SemKVCache:
         if scores is None:
             scores = torch.empty((self.cfg.batch, T), dtype=torch.float32, device=X.device)
         st = X.stride()
-        check(lib().semkv_score_kv_norm(ctypes.byref(self.c), _ptr(X), st[0], st[1], st[2], st[3], T,
+        check(self._lib.semkv_score_kv_norm(self._cref, _ptr(X), st[0], st[1], st[2], st[3], T,
                                         _ptr(scores), _stream()), "semkv_score_kv_norm")
         return scores
 
     def append_kv(self, layer, k, v):
-        check(lib().semkv_append_kv(ctypes.byref(self.c), layer, _ptr(k.contiguous()), _ptr(v.contiguous()),
+        check(self._lib.semkv_append_kv(self._cref, layer, _ptr(k.contiguous()), _ptr(v.contiguous()),
                                     _stream()), "semkv_append_kv")
 
     def append_commit(self, score):
-        check(lib().semkv_append_commit(ctypes.byref(self.c), _ptr(score.contiguous()), _stream()),
+        check(self._lib.semkv_append_commit(self._cref, _ptr(score.contiguous()), _stream()),
               "semkv_append_commit")
 
     def flush(self):
-        check(lib().semkv_flush(ctypes.byref(self.c), _stream()), "semkv_flush")
+        check(self._lib.semkv_flush(self._cref, _stream()), "semkv_flush")
 
     def reset(self):
         """Empty the cache for a new prompt (a multi-turn dialogue's next turn)."""
-        check(lib().semkv_cache_reset(ctypes.byref(self.c), _stream()), "semkv_cache_reset")
+        check(self._lib.semkv_cache_reset(self._cref, _stream()), "semkv_cache_reset")
 
     def workspace_bytes(self):
         n = ctypes.c_size_t()
-        check(lib().semkv_workspace_bytes(ctypes.byref(self.c), ctypes.byref(n)), "semkv_workspace_bytes")
+        check(self._lib.semkv_workspace_bytes(self._cref, ctypes.byref(n)), "semkv_workspace_bytes")
         return n.value
 
     def workspace(self):
@@ -189,7 +207,7 @@ class SemKVCache:
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
         ws = self.workspace() if workspace is None else workspace
-        check(lib().semkv_decode_attn(ctypes.byref(self.c), layer, _ptr(q), _ptr(out), _ptr(ws),
+        check(self._lib.semkv_decode_attn(self._cref, layer, _ptr(q), _ptr(out), _ptr(ws),
                                       ws.numel() * ws.element_size(), _stream()), "semkv_decode_attn")
         return out
 
@@ -200,7 +218,7 @@ class SemKVCache:
         q = q.contiguous()
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-        check(lib().semkv_decode_attn_noalloc(ctypes.byref(self.c), layer, _ptr(q), _ptr(out), _stream()),
+        check(self._lib.semkv_decode_attn_noalloc(self._cref, layer, _ptr(q), _ptr(out), _stream()),
               "semkv_decode_attn_noalloc")
         return out
 
@@ -212,7 +230,7 @@ class SemKVCache:
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
         ws = self.workspace() if workspace is None else workspace
-        check(lib().semkv_append_decode(ctypes.byref(self.c), layer, _ptr(k.contiguous()), _ptr(v.contiguous()),
+        check(self._lib.semkv_append_decode(self._cref, layer, _ptr(k.contiguous()), _ptr(v.contiguous()),
                                         _ptr(q), _ptr(out), _ptr(ws), ws.numel() * ws.element_size(), _stream()),
               "semkv_append_decode")
         return out
