@@ -2,11 +2,14 @@
 // append and the block close of generated tokens (Alg. 2), for gfx950.
 //
 // One workgroup (256 threads) builds one 64-slot record of one pool of one
-// (sequence, layer, kv head) unit.  Four consecutive lanes own one token row:
-// lane q holds channels [32q, 32q+32).  Codes go to LDS, then each thread packs
+// (sequence, layer, kv head) unit.  Four lanes own one token row (consecutive
+// lanes, or for the rotating bases lanes 16 apart): quarter q loads channels
+// [32q, 32q+32).  Codes go to LDS, then each thread packs
 // whole segments (Sec. 4.1 mixed-radix symbols) into the LDS body with atomic
 // ORs, and the record is written with 16-byte stores.
 #include <hip/hip_fp16.h>
+
+#include <type_traits>
 
 #include "semkv_internal.h"
 
@@ -44,6 +47,17 @@ __device__ inline float sqrt_rn(float a) {
   return r;
 }
 
+// fp16 of the correctly rounded fp32 square root of a >= 0: the hardware's
+// root is within one ulp, so only where its neighbours two ulps away round to
+// different fp16 values (one row in two thousand) is the exact root needed.
+__device__ inline uint16_t sqrt_f16(float a) {
+  const float r = __builtin_amdgcn_sqrtf(a);
+  const uint32_t b = __float_as_uint(r);
+  const uint16_t lo = f2h(__uint_as_float(b - 2u)), hi = f2h(__uint_as_float(b + 2u));
+  if (lo == hi && b > 2u) return lo;         // a = 0, infinities and NaN take the exact way
+  return f2h(sqrt_rn(a));
+}
+
 // A row quarter (32 fp16 values) as fp32, and whether any is inf or NaN (the
 // largest magnitude bit pattern, by a packed 16-bit max, reaches 0x7C00).
 __device__ inline void load_quarter(const uint16_t* src, float x[32], bool& nonfinite) {
@@ -64,15 +78,14 @@ __device__ inline void load_quarter(const uint16_t* src, float x[32], bool& nonf
   nonfinite |= big.x >= 0x7C00u || big.y >= 0x7C00u;
 }
 
-// The value of lane (this lane xor 1), xor 2, or of lane 0 of this lane's
-// quad: exact DPP moves within a quad at full VALU rate.  Every lane has a
+// The value of lane (this lane xor 1) or xor 2: exact DPP moves within a quad at full VALU rate.  Every lane has a
 // source lane, so the move needs no prior value (none to materialize, and the
 // compiler may fold the move into the add that uses it).
 template <int CTRL>
 __device__ inline float quad_mov(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kQuadLane0 = 0x00;
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;
 
 // Asymmetric affine quantizer (Sec. 4.1) of one row quarter; the min/max of a
 // group of G channels is combined over the G/32 lanes holding it.  Returns
@@ -116,7 +129,8 @@ __device__ uint32_t affine_quarter(const float x[32], int G, uint32_t code[8]) {
   return uint32_t(s16) | (uint32_t(f2h(zero)) << 16);
 }
 
-// H diag(sign) x of one row quarter: sign flip, then the unnormalized
+// H diag(sign) x of one row quarter (the dequantizer's layout: a row's
+// quarters in the four lanes of a quad): sign flip, then the unnormalized
 // Walsh-Hadamard transform, stages 1..16 inside the lane and 32, 64 across
 // the lanes of the row's quad.
 __device__ inline void rotate_quarter(const float x[32], int q, uint32_t sbits, float u[32]) {
@@ -146,40 +160,169 @@ __device__ inline void rotate_quarter(const float x[32], int q, uint32_t sbits, 
   }
 }
 
-// TurboQuant-MSE base (Sec. 4.9) of one row quarter: the rotation, the row
-// norm by a fixed pairwise tree, one fp16 scalar, and Lloyd-Max threshold
-// codes.  Returns rho bits.
+// ---- rows of the rotating bases while they are quantized
+// A token row sits in the lanes l, l + 16, l + 32, l + 48 of a wave: lane
+// quarter q = lane / 16 loads channels [32 q, 32 q + 32).  The two stages that
+// cross lanes then swap 16-lane rows between two registers
+// (v_permlane16_swap, v_permlane32_swap): one register gets both lower halves,
+// the other both upper ones, and a butterfly is an add and a subtract with no
+// sign flips and no wait states, 1.5 instructions per value and stage; a
+// quad's lane exchange by DPP took two and the wait states of its hazards.
+// The lanes then hold other channels than they loaded (rot_channel).
+// Bound by vector instructions (tq: the VALU issues one per 3.4 cycles, about
+// what four waves reach).  With the signs applied to packed fp16 pairs, the
+// norm's tree by the same swaps, thresholds as clamped multiply-adds and the
+// finiteness check on one rotated value, ranking and quantizing 131072 tokens
+// of 8 layers at 4/3 levels went from 1.53 to 1.30 ms, 3 x 10007 tokens of the
+// rotated affine base from 314 to 288 us.
+// The swaps are written in place (the compiler's own intrinsic copied both
+// registers first, 2 moves a swap) and four at a time behind the two wait
+// states that a swap needs after a vector write of its registers.  Called with
+// the row's four lanes active.
+__device__ inline void swap16(float& a, float& b) {          // a: both even rows of 16, b: both odd ones
+  __asm__("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ inline void swap32(float& a, float& b) {          // a: both lower halves of 32, b: both upper ones
+  __asm__("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ inline void swap16x4(float& a0, float& b0, float& a1, float& b1, float& a2, float& b2, float& a3, float& b3) {
+  __asm__("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3\n\t"
+          "v_permlane16_swap_b32 %4, %5\n\tv_permlane16_swap_b32 %6, %7"
+          : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1), "+v"(a2), "+v"(b2), "+v"(a3), "+v"(b3));
+}
+__device__ inline void swap32x4(float& a0, float& b0, float& a1, float& b1, float& a2, float& b2, float& a3, float& b3) {
+  __asm__("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\t"
+          "v_permlane32_swap_b32 %4, %5\n\tv_permlane32_swap_b32 %6, %7"
+          : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1), "+v"(a2), "+v"(b2), "+v"(a3), "+v"(b3));
+}
+// the value of f over the four lanes of a row, in all of them
+template <class F>
+__device__ inline float row_reduce(float v, F f) {
+  float w = v;
+  swap16(v, w);
+  v = f(v, w);
+  w = v;
+  swap32(v, w);
+  return f(v, w);
+}
+
+// Sign masks of a row quarter's 16 fp16 pairs.
+__device__ inline void sign_masks(uint32_t sbits, uint32_t m[16]) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint32_t t = i < 8 ? sbits << (15 - 2 * i) : sbits >> (2 * i - 15);   // bits 2i, 2i + 1 at 15, 16
+    m[i] = (t & 0x8000u) | ((t << 15) & 0x80000000u);
+  }
+}
+
+// diag(sign) x of a row quarter as fp32 (zeros for a row that is not there)
+__device__ inline void load_signed(const uint16_t* src, bool valid, const uint32_t m[16], float x[32]) {
+  const uint4* p = reinterpret_cast<const uint4*>(src);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint4 w = valid ? p[k] : make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t d[4] = {w.x ^ m[4 * k], w.y ^ m[4 * k + 1], w.z ^ m[4 * k + 2], w.w ^ m[4 * k + 3]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[8 * k + 2 * e] = h2f(uint16_t(d[e] & 0xFFFFu));
+      x[8 * k + 2 * e + 1] = h2f(uint16_t(d[e] >> 16));
+    }
+  }
+}
+
+// H x of the row, stages 1..16 inside the lane, 32 and 64 across its lanes,
+// each as lower + upper and lower - upper.  Register 16 q0 + 8 q1 + i then holds
+// channel rot_channel(lane) + 64 q1 + 32 q0 + i.
+__device__ inline int rot_channel(int lane) { return (lane & 16) + ((lane & 32) >> 2); }
+__device__ inline void rotate_row(float u[32]) {
+#pragma unroll
+  for (int h = 1; h < 32; h <<= 1)
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+      if (!(i & h)) {
+        const float p = u[i], r = u[i + h];
+        u[i] = p + r;
+        u[i + h] = p - r;
+      }
+#pragma unroll
+  for (int i = 0; i < 16; i += 4) {                          // h = 32: lane quarters 0-1, 2-3
+    swap16x4(u[i], u[i + 16], u[i + 1], u[i + 17], u[i + 2], u[i + 18], u[i + 3], u[i + 19]);
+#pragma unroll
+    for (int k = i; k < i + 4; ++k) {
+      const float p = u[k], r = u[k + 16];
+      u[k] = p + r;
+      u[k + 16] = p - r;
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < 32; g += 16)
+#pragma unroll
+    for (int i = g; i < g + 8; i += 4) {                     // h = 64: lane halves
+      swap32x4(u[i], u[i + 8], u[i + 1], u[i + 9], u[i + 2], u[i + 10], u[i + 3], u[i + 11]);
+#pragma unroll
+      for (int k = i; k < i + 4; ++k) {
+        const float p = u[k], r = u[k + 8];
+        u[k] = p + r;
+        u[k + 8] = p - r;
+      }
+    }
+}
+
+// The row norm's square: the squares summed by the fixed pairwise tree
+// (channels 64 apart, then 32, 16, ..., 1), in every lane of the row.
+__device__ inline float row_square_sum(const float x[32]) {
+  float a[16];
+#pragma unroll
+  for (int m = 0; m < 16; m += 4) {                          // 64: i = 2 m + lane half
+    float q[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) q[k] = x[2 * m + k] * x[2 * m + k];
+    swap32x4(q[0], q[1], q[2], q[3], q[4], q[5], q[6], q[7]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[m + k] = q[2 * k] + q[2 * k + 1];
+  }
+#pragma unroll
+  for (int m = 0; m < 8; m += 4) {                           // 32: i = 4 m + 2 (odd row) + lane half
+    swap16x4(a[2 * m], a[2 * m + 1], a[2 * m + 2], a[2 * m + 3], a[2 * m + 4], a[2 * m + 5], a[2 * m + 6], a[2 * m + 7]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[m + k] = a[2 * (m + k)] + a[2 * (m + k) + 1];
+  }
+#pragma unroll
+  for (int h = 4; h >= 1; h >>= 1)                           // 16, 8, 4
+#pragma unroll
+    for (int m = 0; m < h; ++m) a[m] = a[m] + a[m + h];
+  return row_reduce(a[0], [](float p, float r) { return p + r; });   // 2, 1
+}
+
+// TurboQuant-MSE base (Sec. 4.9) of one row (signed, not yet rotated, in u):
+// the row norm, one fp16 scalar, and Lloyd-Max threshold codes of the rotated
+// row.  A threshold's step is one clamped multiply-add: (u - t) 2^64 is 0 or
+// below where u <= t, and at least 1 where u > t (u and t differ by at least
+// 2^-49: u is a multiple of 2^-24, t has 24 significant bits and is 0 or at
+// least 2^-26).  Returns rho bits.
 template <int L>
-__device__ uint16_t tq_quarter(const float x[32], int q, const uint32_t* sw, const float* tau,
-                               uint32_t code[8]) {
-  float u[32], a[32];
-  rotate_quarter(x, q, sw[q], u);
-#pragma unroll
-  for (int i = 0; i < 32; ++i) a[i] = x[i] * x[i];
-#pragma unroll
-  for (int i = 0; i < 32; ++i) a[i] = a[i] + quad_mov<kQuadXor2>(a[i]);   // h = 64 (lanes 0,1 keep)
-#pragma unroll
-  for (int i = 0; i < 32; ++i) a[i] = a[i] + quad_mov<kQuadXor1>(a[i]);   // h = 32 (lane 0 keeps)
-#pragma unroll
-  for (int h = 16; h >= 1; h >>= 1)
-#pragma unroll
-    for (int i = 0; i < h; ++i) a[i] = a[i] + a[i + h];
-  uint16_t r16 = f2h(sqrt_rn(a[0]));
+__device__ uint16_t tq_row(float u[32], const float* tau, uint32_t code[8]) {
+  uint16_t r16 = sqrt_f16(row_square_sum(u));
   if ((r16 & 0x7FFFu) == 0x7C00u) r16 = 0x7BFFu;       // saturate to 65504
-  r16 = uint16_t(__float_as_uint(quad_mov<kQuadLane0>(__uint_as_float(uint32_t(r16)))));
-  float rf = h2f(r16);
+  rotate_row(u);
+  const float rf = h2f(r16);
+  constexpr float kBig = 18446744073709551616.0f;      // 2^64
   float thr[L - 1];
 #pragma unroll
-  for (int k = 0; k < L - 1; ++k) thr[k] = rf * tau[k];
+  for (int k = 0; k < L - 1; ++k) thr[k] = -(rf * tau[k]) * kBig;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     uint32_t w = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      uint32_t c = 0;
+      float c = 0.0f;
 #pragma unroll
-      for (int t = 0; t < L - 1; ++t) c += u[4 * k + e] > thr[t] ? 1u : 0u;
-      w |= c << (8 * e);
+      for (int t = 0; t < L - 1; ++t) {
+        float f;
+        __asm__("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(f) : "v"(u[4 * k + e]), "s"(kBig), "v"(thr[t]));
+        c = t == 0 ? f : c + f;
+      }
+      w = __builtin_amdgcn_cvt_pk_u8_f32(c, e, w);
     }
     code[k] = w;
   }
@@ -190,65 +333,110 @@ __device__ uint16_t tq_quarter(const float x[32], int q, const uint32_t* sw, con
 // y = H diag(sign) x / 16 (the division is exact), then per group of G
 // rotated coordinates zero = fp16(min y) (-0 stored as +0) and scale =
 // fp16(max(0, (max y - zero) / (L-1))), each saturated at +-65504, codes
-// against the stored pair.
-// Returns {scale, zero} as fp16 bits (low half = scale).
-template <int L>
-__device__ uint32_t rot_affine_quarter(const float x[32], int q, const uint32_t* sw, int G, uint32_t code[8]) {
-  float y[32];
-  rotate_quarter(x, q, sw[q], y);
-  float mn = INFINITY, mx = -INFINITY;
+// against the stored pair.  u: H diag(sign) x.  meta[g]: {scale, zero} of
+// group g as fp16 bits (low half = scale).
+template <int L, int G>
+__device__ inline void rot_affine_row(const float u[32], uint32_t meta[128 / G], uint32_t code[8]) {
+  constexpr int NG = 128 / G;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    y[i] *= 0.0625f;
-    mn = fminf(mn, y[i]);
-    mx = fmaxf(mx, y[i]);
-  }
-  if (G >= 64) {
-    mn = fminf(mn, quad_mov<kQuadXor1>(mn));
-    mx = fmaxf(mx, quad_mov<kQuadXor1>(mx));
-  }
-  if (G >= 128) {
-    mn = fminf(mn, quad_mov<kQuadXor2>(mn));
-    mx = fmaxf(mx, quad_mov<kQuadXor2>(mx));
-  }
-  // rotated coordinates reach 128 * 65504 / 16 in magnitude: both parameters
-  // saturate at +-65504
-  uint16_t z16 = sat16(f2h(mn));
-  z16 = z16 == 0x8000u ? uint16_t(0) : z16;
-  const float zero = h2f(z16);
-  const float s32 = __fdiv_rn(mx - zero, float(L - 1));
-  const uint16_t s16 = sat16(f2h(s32 > 0.0f ? s32 : 0.0f));
-  const float sf = h2f(s16);
-  const float inv = sf == 0.0f ? 0.0f : __fdiv_rn(1.0f, sf);
+  for (int g = 0; g < NG; ++g) {
+    // registers of the group: 16 q0 + 8 q1 + i, i < 8
+    float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    uint32_t w = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {                         // clamp, then round in the convert
-      const float c = fminf(fmaxf((y[4 * k + e] - zero) * inv, 0.0f), float(L - 1));
-      w = __builtin_amdgcn_cvt_pk_u8_f32(c, e, w);
+    for (int i = 0; i < 32; ++i) {
+      const int q0 = i >> 4, q1 = (i >> 3) & 1;
+      if ((64 * q1 + 32 * q0) / G != g) continue;
+      mn = fminf(mn, u[i]);
+      mx = fmaxf(mx, u[i]);
     }
-    code[k] = w;
+    // the exact 1/16 of the extremes; of the values in the code's subtraction
+    mn = row_reduce(mn, [](float p, float r) { return fminf(p, r); }) * 0.0625f;
+    mx = row_reduce(mx, [](float p, float r) { return fmaxf(p, r); }) * 0.0625f;
+    // rotated coordinates reach 128 * 65504 / 16 in magnitude: both parameters
+    // saturate at +-65504
+    uint16_t z16 = sat16(f2h(mn));
+    z16 = z16 == 0x8000u ? uint16_t(0) : z16;
+    const float zero = h2f(z16);
+    const float s32 = __fdiv_rn(mx - zero, float(L - 1));
+    const uint16_t s16 = sat16(f2h(s32 > 0.0f ? s32 : 0.0f));
+    const float sf = h2f(s16);
+    const float inv = sf == 0.0f ? 0.0f : __fdiv_rn(1.0f, sf);
+    meta[g] = uint32_t(s16) | (uint32_t(z16) << 16);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int q0 = k >> 2, q1 = (k >> 1) & 1;
+      if ((64 * q1 + 32 * q0) / G != g) continue;
+      uint32_t w = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {                       // clamp, then round in the convert
+        const float c = fminf(fmaxf(fmaf(u[4 * k + e], 0.0625f, -zero) * inv, 0.0f), float(L - 1));
+        w = __builtin_amdgcn_cvt_pk_u8_f32(c, e, w);
+      }
+      code[k] = w;
+    }
   }
-  return uint32_t(s16) | (uint32_t(z16) << 16);
 }
 
-// Quantize the quarter row held by this lane and write its metadata.
+// The row and the quarter of it that a thread of the workgroup holds while
+// quantizing: neighbouring lanes for the unrotated base, lanes 16 apart for
+// the rotating ones.
+template <int BASE>
+__device__ inline int row_of_thread(int tid) { return BASE == 0 ? tid >> 2 : (tid >> 6) * 16 + (tid & 15); }
+template <int BASE>
+__device__ inline int quarter_of_thread(int tid) { return BASE == 0 ? tid & 3 : (tid >> 4) & 3; }
+
+// Quantize a row's K or V: every thread of the row writes its codes to the
+// row of the code array (zeros for a row that is not there) and the metadata
+// of its share of the groups.  m: the rotating bases' sign masks.  bad: a value
+// was not finite.
 template <int BASE, int L>
-__device__ void quantize_quarter(const PoolGeom& g, const float x[32], int q, int layer, int kvh,
-                                 const float* tau, uint32_t code[8], uint8_t* meta_dst, int slot,
-                                 bool valid) {
-  if (BASE != 1) {
-    const uint32_t m = BASE == 0 ? affine_quarter<L>(x, g.G, code)
-                                 : rot_affine_quarter<L>(x, q, g.signs + (int64_t(layer) * g.n_kv_heads + kvh) * 4,
-                                                         g.G, code);
-    int per = g.G / 32;
-    if (q % per == 0)
-      reinterpret_cast<uint32_t*>(meta_dst)[(q / per) * kSlots + slot] = valid ? m : 0u;
+__device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid, int q, const uint32_t m[16],
+                             const float* tau, uint8_t* codes, uint8_t* meta_dst, int slot, bool& bad) {
+  if constexpr (BASE == 0) {
+    float x[32];
+    uint32_t code[8];
+    if (valid) {
+      load_quarter(src, x, bad);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) x[i] = 0.0f;
+    }
+    const uint32_t w = affine_quarter<L>(x, g.G, code);
+    const int per = g.G / 32;
+    if (q % per == 0) reinterpret_cast<uint32_t*>(meta_dst)[(q / per) * kSlots + slot] = valid ? w : 0u;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(codes + 32 * q);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dst[i] = valid ? code[i] : 0u;
   } else {
-    const uint32_t* sw = g.signs + (int64_t(layer) * g.n_kv_heads + kvh) * 4;
-    uint16_t r = tq_quarter<L>(x, q, sw, tau, code);
-    if (q == 0) reinterpret_cast<uint16_t*>(meta_dst)[slot] = valid ? r : uint16_t(0);
+    float u[32];
+    uint32_t code[8];
+    load_signed(src, valid, m, u);
+    if constexpr (BASE == 1) {
+      const uint16_t r = tq_row<L>(u, tau, code);
+      if (q == 0) reinterpret_cast<uint16_t*>(meta_dst)[slot] = valid ? r : uint16_t(0);
+    } else {
+      rotate_row(u);
+      auto affine = [&](auto GC) {
+        constexpr int G = decltype(GC)::value;
+        uint32_t w[128 / G];
+        rot_affine_row<L, G>(u, w, code);
+#pragma unroll
+        for (int i = 0; i < 128 / G; ++i)
+          if (q == i) reinterpret_cast<uint32_t*>(meta_dst)[i * kSlots + slot] = valid ? w[i] : 0u;
+      };
+      if (g.G == 128) affine(std::integral_constant<int, 128>{});
+      else if (g.G == 64) affine(std::integral_constant<int, 64>{});
+      else affine(std::integral_constant<int, 32>{});
+    }
+    // an infinity or a NaN of the row reaches every rotated coordinate, and
+    // finite rows stay finite (128 * 65504)
+    bad |= (__float_as_uint(u[0]) & 0x7F800000u) == 0x7F800000u;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(codes + rot_channel(int(threadIdx.x) & 63));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int q0 = k >> 2, q1 = (k >> 1) & 1;
+      dst[(64 * q1 + 32 * q0) / 4 + (k & 1)] = valid ? code[k] : 0u;
+    }
   }
 }
 
@@ -362,10 +550,12 @@ struct Lds {
 template <int BASE, int L>
 __device__ void prefill_record(const QuantArgs& a, Lds& s, int pool, int tile, int b, int l, int h) {
   const PoolGeom& g = a.g;
-  int tid = threadIdx.x, r = tid >> 2, q = tid & 3;
+  const int tid = threadIdx.x, r = row_of_thread<BASE>(tid), q = quarter_of_thread<BASE>(tid);
   int64_t slot = int64_t(tile) * kSlots + r;
   bool valid = slot < a.n_pool[pool];
   int tok = valid ? a.idx[pool][int64_t(b) * a.n_pool[pool] + slot] : 0;
+  uint32_t m[16];
+  if constexpr (BASE != 0) sign_masks(g.signs[(int64_t(l) * g.n_kv_heads + h) * 4 + q], m);
   if (tok < 0 || tok >= a.T) {             // a slot list not produced by semkv_rank
     if (valid) atomicOr(g.status, 4);
     tok = 0;
@@ -375,21 +565,10 @@ __device__ void prefill_record(const QuantArgs& a, Lds& s, int pool, int tile, i
   for (int i = tid; i < kMaxBodyWords + 8; i += 256) s.bk[i] = s.bv[i] = 0u;
   bool bad = false;
   const int64_t base_off = int64_t(l) * a.sL + int64_t(b) * a.sB + int64_t(h) * a.sH + int64_t(tok) * a.sT + 32 * q;
-  float x[32];
-  uint32_t code[8];
 #pragma unroll
-  for (int kv = 0; kv < 2; ++kv) {
-    if (valid) {
-      load_quarter((kv ? a.V : a.K) + base_off, x, bad);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 32; ++i) x[i] = 0.0f;
-    }
-    quantize_quarter<BASE, L>(g, x, q, l, h, g.tau[pool], code, rec + 2 * tb + kv * g.meta_bytes, r, valid);
-    uint32_t* dst = reinterpret_cast<uint32_t*>((kv ? s.cv : s.ck) + r * kPitch + 32 * q);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) dst[i] = valid ? code[i] : 0u;
-  }
+  for (int kv = 0; kv < 2; ++kv)
+    quantize_row<BASE, L>(g, (kv ? a.V : a.K) + base_off, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
+                          rec + 2 * tb + kv * g.meta_bytes, r, bad);
   if (bad && valid) atomicOr(g.status, 2);
   __syncthreads();
   pack_record<L>(s.ck, s.cv, s.bk, s.bv);
@@ -413,7 +592,7 @@ template <int BASE, int L>
 __device__ void close_record(const CloseArgs& a, Lds& s, const int* row_of, int m, int pool,
                              int tile, int b, int l, int h) {
   const PoolGeom& g = a.g;
-  int tid = threadIdx.x, r = tid >> 2, q = tid & 3;
+  const int tid = threadIdx.x, r = row_of_thread<BASE>(tid), q = quarter_of_thread<BASE>(tid);
   constexpr int tb = tile_bytes(L);
   uint8_t* rec = g.pools + unit_offset(g, b, l, h) + (pool ? g.lo_offset : 0) + int64_t(tile) * g.rec_bytes[pool];
   int64_t first = int64_t(tile) * kSlots;
@@ -444,21 +623,12 @@ __device__ void close_record(const CloseArgs& a, Lds& s, const int* row_of, int 
   bool bad = false;
   if (fresh) {
     const uint16_t* src = a.tail + ((((int64_t(b) * g.n_layers + l) * g.n_kv_heads + h) * 2) * kSlots + row) * kD + 32 * q;
-    float x[32];
-    uint32_t code[8];
+    uint32_t m[16];
+    if constexpr (BASE != 0) sign_masks(g.signs[(int64_t(l) * g.n_kv_heads + h) * 4 + q], m);
 #pragma unroll
-    for (int kv = 0; kv < 2; ++kv) {
-      if (valid) {
-        load_quarter(src + kv * kSlots * kD, x, bad);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 32; ++i) x[i] = 0.0f;
-      }
-      quantize_quarter<BASE, L>(g, x, q, l, h, g.tau[pool], code, rec + 2 * tb + kv * g.meta_bytes, r, valid);
-      uint32_t* dst = reinterpret_cast<uint32_t*>((kv ? s.cv : s.ck) + r * kPitch + 32 * q);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) dst[i] = valid ? code[i] : 0u;
-    }
+    for (int kv = 0; kv < 2; ++kv)
+      quantize_row<BASE, L>(g, src + kv * kSlots * kD, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
+                            rec + 2 * tb + kv * g.meta_bytes, r, bad);
   }
   if (bad && valid) atomicOr(g.status, 2);
   __syncthreads();

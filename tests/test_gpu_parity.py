@@ -334,6 +334,31 @@ def test_status_word_reports_nan_and_inf():
     assert cache2.status() & 2
 
 
+@pytest.mark.parametrize("base,lh,ll,G", [("tq", 4, 3, 128), ("rot_affine", 6, 5, 128), ("rot_affine", 5, 4, 32)])
+@pytest.mark.parametrize("channel", [0, 31, 32, 64, 127])
+def test_rotated_bases_report_nonfinite_rows(base, lh, ll, G, channel):
+    """One NaN or infinity in any lane's share of a row, or two opposite
+    infinities, reaches the status word; rows at the largest finite fp16
+    magnitude do not."""
+    import torch
+    T = 70
+    cfgw = get_config(0, base=base, L_hi=lh, L_lo=ll, group=G, n_kv_heads=1, n_q_heads=4, r_num=1, r_den=2)
+    K, V = synth.layer_kv(cfgw, 0, T)
+    for value, where in ((65504.0, "all"), (np.inf, "K"), (-np.inf, "V"), (np.nan, "K"), ("both", "V")):
+        cache = U.make_cache(cfgw, T, n_layers=1, max_new=0)
+        hi, lo = cache.rank(torch.from_numpy(synth.all_scores(cfgw, T)).cuda())
+        k, v = K.copy(), V.copy()
+        if where == "all":
+            k[0, 0, 69] = np.where(np.arange(128) % 3 == 0, -value, value)
+        elif value == "both":
+            v[0, 0, 69, channel], v[0, 0, 69, channel ^ 1] = np.inf, -np.inf
+        else:
+            (k if where == "K" else v)[0, 0, 69, channel] = value
+        cache.quantize_pack(0, torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda(), hi, lo)
+        torch.cuda.synchronize()
+        assert cache.status() == (0 if where == "all" else 2), (value, where)
+
+
 def test_tq_norm_rounding_edge_rows():
     """Rows whose norm sits at an fp16 rounding edge (a square root one ulp off
     would store a different norm): packed records bit-exact."""
