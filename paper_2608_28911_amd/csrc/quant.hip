@@ -58,26 +58,6 @@ __device__ inline uint16_t sqrt_f16(float a) {
   return f2h(sqrt_rn(a));
 }
 
-// A row quarter (32 fp16 values) as fp32, and whether any is inf or NaN (the
-// largest magnitude bit pattern, by a packed 16-bit max, reaches 0x7C00).
-__device__ inline void load_quarter(const uint16_t* src, float x[32], bool& nonfinite) {
-  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-  const uint4* p = reinterpret_cast<const uint4*>(src);
-  u16x2 big = u16x2{0, 0};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    uint4 w = p[k];
-    uint32_t d[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      x[8 * k + 2 * e] = h2f(uint16_t(d[e] & 0xFFFFu));
-      x[8 * k + 2 * e + 1] = h2f(uint16_t(d[e] >> 16));
-      big = __builtin_elementwise_max(big, __builtin_bit_cast(u16x2, d[e] & 0x7FFF7FFFu));
-    }
-  }
-  nonfinite |= big.x >= 0x7C00u || big.y >= 0x7C00u;
-}
-
 // The value of lane (this lane xor 1) or xor 2: exact DPP moves within a quad at full VALU rate.  Every lane has a
 // source lane, so the move needs no prior value (none to materialize, and the
 // compiler may fold the move into the add that uses it).
@@ -87,16 +67,46 @@ __device__ inline float quad_mov(float x) {
 }
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;
 
+// Minimum and maximum of a row quarter (32 fp16 values), two values at a time
+// and NaN if any is one: the quarter's finiteness comes with them.
+typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
+__device__ inline void quarter_range(const uint32_t d[16], float& mn, float& mx) {
+  h16x2 a = __builtin_bit_cast(h16x2, d[0]), b = a;
+#pragma unroll
+  for (int i = 1; i < 15; i += 2) {
+    const h16x2 x = __builtin_bit_cast(h16x2, d[i]), y = __builtin_bit_cast(h16x2, d[i + 1]);
+    a = __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, x), y);
+    b = __builtin_elementwise_maximum(__builtin_elementwise_maximum(b, x), y);
+  }
+  const h16x2 z = __builtin_bit_cast(h16x2, d[15]);
+  a = __builtin_elementwise_minimum(a, z);
+  b = __builtin_elementwise_maximum(b, z);
+  mn = float(__builtin_elementwise_minimum(a.x, a.y));
+  mx = float(__builtin_elementwise_maximum(b.x, b.y));
+}
+
 // Asymmetric affine quantizer (Sec. 4.1) of one row quarter; the min/max of a
 // group of G channels is combined over the G/32 lanes holding it.  Returns
 // {scale, zero} as fp16 bits (low half = scale).
 template <int L>
-__device__ uint32_t affine_quarter(const float x[32], int G, uint32_t code[8]) {
-  float mn = x[0], mx = x[0];
+__device__ uint32_t affine_quarter(const uint32_t d[16], int G, uint32_t code[8], bool& nonfinite) {
+  float x[32];
 #pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    mn = fminf(mn, x[i]);
-    mx = fmaxf(mx, x[i]);
+  for (int i = 0; i < 16; ++i) {
+    x[2 * i] = h2f(uint16_t(d[i] & 0xFFFFu));
+    x[2 * i + 1] = h2f(uint16_t(d[i] >> 16));
+  }
+  float mn, mx;
+  quarter_range(d, mn, mx);
+  const bool odd = !(mn > -INFINITY && mx < INFINITY);       // an infinity or a NaN (which both carry)
+  nonfinite |= odd;
+  if (odd) {                                                  // the range of the other values
+    mn = mx = x[0];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      mn = fminf(mn, x[i]);
+      mx = fmaxf(mx, x[i]);
+    }
   }
   if (G >= 64) {
     mn = fminf(mn, quad_mov<kQuadXor1>(mn));
@@ -173,8 +183,8 @@ __device__ inline void rotate_quarter(const float x[32], int q, uint32_t sbits, 
 // what four waves reach).  With the signs applied to packed fp16 pairs, the
 // norm's tree by the same swaps, thresholds as clamped multiply-adds and the
 // finiteness check on one rotated value, ranking and quantizing 131072 tokens
-// of 8 layers at 4/3 levels went from 1.53 to 1.30 ms, 3 x 10007 tokens of the
-// rotated affine base from 314 to 288 us.
+// of 8 layers at 4/3 levels went from 1.52 to 1.28 ms, 3 x 10007 tokens of the
+// rotated affine base from 305 to 289 us.
 // The swaps are written in place (the compiler's own intrinsic copied both
 // registers first, 2 moves a swap) and four at a time behind the two wait
 // states that a swap needs after a vector write of its registers.  Called with
@@ -393,15 +403,13 @@ template <int BASE, int L>
 __device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid, int q, const uint32_t m[16],
                              const float* tau, uint8_t* codes, uint8_t* meta_dst, int slot, bool& bad) {
   if constexpr (BASE == 0) {
-    float x[32];
-    uint32_t code[8];
-    if (valid) {
-      load_quarter(src, x, bad);
-    } else {
+    uint32_t d[16], code[8];
 #pragma unroll
-      for (int i = 0; i < 32; ++i) x[i] = 0.0f;
+    for (int k = 0; k < 4; ++k) {
+      const uint4 p = valid ? reinterpret_cast<const uint4*>(src)[k] : make_uint4(0u, 0u, 0u, 0u);
+      d[4 * k] = p.x, d[4 * k + 1] = p.y, d[4 * k + 2] = p.z, d[4 * k + 3] = p.w;
     }
-    const uint32_t w = affine_quarter<L>(x, g.G, code);
+    const uint32_t w = affine_quarter<L>(d, g.G, code, bad);
     const int per = g.G / 32;
     if (q % per == 0) reinterpret_cast<uint32_t*>(meta_dst)[(q / per) * kSlots + slot] = valid ? w : 0u;
     uint32_t* dst = reinterpret_cast<uint32_t*>(codes + 32 * q);
@@ -440,12 +448,48 @@ __device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid,
   }
 }
 
+// Symbol of ND codes of base L at bytes O.. of a row of codes: dword reads and
+// four digits per dot product (L^3 fits a byte up to 6 levels; 7 levels take
+// the digits one by one).  Codes past ND meet zero weights.  With a byte read
+// and a multiply-add per code of K instead, and the affine range one fp32 value
+// at a time with a finiteness check of its own, ranking and quantizing 32768
+// tokens of 32 layers took 961 us instead of 936, and 131072 tokens of 8
+// layers on the tq base 1278 instead of 1257.
+template <int L, int O, int ND>
+__device__ __forceinline__ uint32_t row_symbol(const uint32_t* row) {
+  constexpr int sh = O & 3, n1 = (sh + ND + 3) / 4;                    // dwords the codes span
+  const uint32_t d0 = row[O / 4], d1 = n1 > 1 ? row[O / 4 + 1] : 0u, d2 = n1 > 2 ? row[O / 4 + 2] : 0u;
+  const uint32_t c03 = sh ? __builtin_amdgcn_alignbyte(d1, d0, sh) : d0;
+  constexpr uint32_t w03 = 1u | (ND > 1 ? uint32_t(L) << 8 : 0u) | (ND > 2 ? uint32_t(L * L) << 16 : 0u) |
+                           (ND > 3 ? uint32_t(L * L * L) << 24 : 0u);
+  uint32_t v = __builtin_amdgcn_udot4(c03, w03, 0u, false);
+  if constexpr (ND > 4) {
+    const uint32_t c47 = sh ? __builtin_amdgcn_alignbyte(d2, d1, sh) : d1;
+    constexpr uint32_t L4 = uint32_t(L) * L * L * L;
+    if constexpr (L4 < 256u) {               // 2 and 3 levels
+      constexpr uint32_t w47 = L4 | (ND > 5 ? L4 * L << 8 : 0u) | (ND > 6 ? L4 * L * L << 16 : 0u) | (ND > 7 ? L4 * L * L * L << 24 : 0u);
+      v = __builtin_amdgcn_udot4(c47, w47, v, false);
+    } else {                                 // 6 levels: one more code
+      v += __umul24(c47 & 255u, L4);
+    }
+  }
+  return v;
+}
+
 // OR the bits of one segment into an LDS body.  The segment holds symbols
 // p = j, j+4, ... of a line of NV codes: code p*n+i of the line is at
 // codes[(p*n+i)*stride].  J is compile-time: the symbols' widths and bit
 // positions are constants, the line's offset is applied by one funnel shift
-// per word.
-template <int L, int NV, int NL, int J>
+// per word.  ROW: the line is a row of codes (stride 1, 4-byte aligned).
+template <int L, int NV, int NL, bool ROW, int J, int K = 0>
+__device__ __forceinline__ void row_symbols(const uint32_t* row, uint32_t (&v)[16]) {
+  constexpr SegTable<L, NV, NL> t{};
+  if constexpr (K < 16) {
+    if constexpr (t.width[J][K] > 0) v[K] = row_symbol<L, sym_digits(L) * (J + 4 * K), t.ndig[J][K]>(row);
+    row_symbols<L, NV, NL, ROW, J, K + 1>(row, v);
+  }
+}
+template <int L, int NV, int NL, bool ROW, int J>
 __device__ __forceinline__ void pack_segment_j(const uint8_t* codes, int stride, int line, uint32_t* body) {
   constexpr int n = sym_digits(L);
   constexpr SegTable<L, NV, NL> t{};
@@ -455,15 +499,22 @@ __device__ __forceinline__ void pack_segment_j(const uint8_t* codes, int stride,
 #pragma unroll
   for (int k = 0; k < NWD; ++k) w[k] = 0u;
   int nb = 0;
+  constexpr bool DOT = ROW && L != 7;
+  uint32_t sym[16];
+  if constexpr (DOT) row_symbols<L, NV, NL, ROW, J>(reinterpret_cast<const uint32_t*>(codes), sym);
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const int wd = t.width[J][k], nd = t.ndig[J][k];
     if (wd > 0) {
       const int p = J + 4 * k;
       uint32_t v = 0;
+      if constexpr (DOT) {
+        v = sym[k];
+      } else {
 #pragma unroll
-      for (int i = n - 1; i >= 0; --i)
-        if (i < nd) v = v * L + codes[(n * p + i) * stride];
+        for (int i = n - 1; i >= 0; --i)
+          if (i < nd) v = v * L + codes[(n * p + i) * stride];
+      }
       w[nb >> 5] |= v << (nb & 31);
       if ((nb & 31) + wd > 32) w[(nb >> 5) + 1] |= v >> (32 - (nb & 31));
       nb += wd;
@@ -479,13 +530,13 @@ __device__ __forceinline__ void pack_segment_j(const uint8_t* codes, int stride,
   }
 }
 
-template <int L, int NV, int NL>
+template <int L, int NV, int NL, bool ROW>
 __device__ __forceinline__ void pack_segment(const uint8_t* codes, int stride, int line, int j, uint32_t* body) {
   switch (j) {                                          // j is the same for a whole wave
-    case 0: pack_segment_j<L, NV, NL, 0>(codes, stride, line, body); break;
-    case 1: pack_segment_j<L, NV, NL, 1>(codes, stride, line, body); break;
-    case 2: pack_segment_j<L, NV, NL, 2>(codes, stride, line, body); break;
-    default: pack_segment_j<L, NV, NL, 3>(codes, stride, line, body); break;
+    case 0: pack_segment_j<L, NV, NL, ROW, 0>(codes, stride, line, body); break;
+    case 1: pack_segment_j<L, NV, NL, ROW, 1>(codes, stride, line, body); break;
+    case 2: pack_segment_j<L, NV, NL, ROW, 2>(codes, stride, line, body); break;
+    default: pack_segment_j<L, NV, NL, ROW, 3>(codes, stride, line, body); break;
   }
 }
 
@@ -521,11 +572,11 @@ __device__ void unpack_segment(const uint32_t* body, int line, int j, uint8_t* c
 template <int L>
 __device__ __forceinline__ void pack_record(const uint8_t* ck, const uint8_t* cv, uint32_t* bk, uint32_t* bv) {
   int tid = threadIdx.x;
-  pack_segment<L, kD, kSlots>(ck + (tid & 63) * kPitch, 1, tid & 63, tid >> 6, bk);
+  pack_segment<L, kD, kSlots, true>(ck + (tid & 63) * kPitch, 1, tid & 63, tid >> 6, bk);
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     int s = tid + 256 * e;
-    pack_segment<L, kSlots, kD>(cv + (s & 127), kPitch, s & 127, s >> 7, bv);
+    pack_segment<L, kSlots, kD, false>(cv + (s & 127), kPitch, s & 127, s >> 7, bv);
   }
 }
 
