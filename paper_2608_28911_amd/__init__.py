@@ -100,7 +100,7 @@ class SemKVCache:
         self._ws = None
         self._cref = ctypes.byref(self.c)
         self._lib = lib()
-        self._ratio = (self.c.cfg.r_num, self.c.cfg.r_den, self.c.cfg.max_prompt)
+        self._cfg = self.c.cfg               # a view: reads the cache's own configuration
 
     # -- the hot path ------------------------------------------------------
     def rank_sizes(self, T):
@@ -116,9 +116,9 @@ class SemKVCache:
         import torch
         scores = scores.contiguous()
         B, T = scores.shape
-        rn, rd, most = self._ratio
-        if 1 <= T <= most:                   # as rank_sizes, without a call into the library
-            n_hi = rn * T // rd
+        cfg = self._cfg
+        if 1 <= T <= cfg.max_prompt:         # as rank_sizes, without a call into the library
+            n_hi = cfg.r_num * T // cfg.r_den
             n_lo = T - n_hi
         else:
             n_hi, n_lo = self.rank_sizes(T)  # raises

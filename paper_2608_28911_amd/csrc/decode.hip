@@ -86,11 +86,10 @@ __device__ inline void timeline_put(int ev, unsigned long long v) {
 #else
 #define SEMKV_STAMP_FINE(ev) ((void)0)
 #endif
-// 0 start, 1 tables and query operands built, 2 first record in LDS,
-// 3..7 the wave's 1st..5th record done, the next record's data stored in LDS
-// (a 6th and later overwrite 7), 8 the first record's arithmetic done (before
-// the next record's data is waited for), 16..18 inside the first record: the
-// next record's loads issued, scores done, softmax and flush done, 19..21 in
+// 0 start, 1 tables and query operands built, 2 the wave's state set up,
+// 3..7 the wave's 1st..5th record done (a 6th and later overwrite 7), 8 the
+// first record's arithmetic done, 16..18 inside the first record: its metadata
+// in LDS, scores done, softmax and flush done, 19..21 in
 // the prologue: tables written, query value in hand, query runs done,
 // 9 the wave's records done, 10 workgroup partial merged, 11 partial stored,
 // 12 split counter taken, 13 the last workgroup's merge done; counts: 14 the

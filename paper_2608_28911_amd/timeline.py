@@ -21,12 +21,12 @@ from . import _abi as A
 from .build import LIB_TIMELINE
 
 WGS, WAVES, EVENTS = 4096, 16, 32
-NAMES = {0: "start", 1: "tables + query operands", 2: "first record in LDS",
-         8: "record 1 arithmetic done", 3: "record 1 done (next record in LDS)",
+NAMES = {0: "start", 1: "tables + query operands", 2: "wave state set up",
+         8: "record 1 arithmetic done", 3: "record 1 done",
          4: "record 2 done", 5: "record 3 done", 6: "record 4 done", 7: "record 5+ done",
          9: "wave's records done", 10: "workgroup partial merged",
          11: "partial stored", 12: "split counter taken", 13: "last workgroup's merge done",
-         16: "record 1: next record's loads issued", 17: "record 1: scores done",
+         16: "record 1: metadata in LDS", 17: "record 1: scores done",
          18: "record 1: softmax and flush done", 19: "prologue: tables written",
          20: "prologue: query value in hand", 21: "prologue: query runs done"}
 ORDER = [0, 19, 20, 21, 1, 2, 16, 17, 18, 8, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13]
