@@ -34,6 +34,7 @@ def _stream():
 
 
 def _ptr(t):
+    """The tensor's address: an integer, which keeps nothing alive."""
     return t.data_ptr()
 
 
@@ -172,12 +173,12 @@ class SemKVCache:
         return scores
 
     def append_kv(self, layer, k, v):
-        check(self._lib.semkv_append_kv(self._cref, layer, _ptr(k.contiguous()), _ptr(v.contiguous()),
-                                    _stream()), "semkv_append_kv")
+        k, v = k.contiguous(), v.contiguous()    # named: each copy lives until the call has returned
+        check(self._lib.semkv_append_kv(self._cref, layer, _ptr(k), _ptr(v), _stream()), "semkv_append_kv")
 
     def append_commit(self, score):
-        check(self._lib.semkv_append_commit(self._cref, _ptr(score.contiguous()), _stream()),
-              "semkv_append_commit")
+        score = score.contiguous()
+        check(self._lib.semkv_append_commit(self._cref, _ptr(score), _stream()), "semkv_append_commit")
 
     def flush(self):
         check(self._lib.semkv_flush(self._cref, _stream()), "semkv_flush")
@@ -226,13 +227,12 @@ class SemKVCache:
         """Fused append + decode of one layer: k, v fp16 [B, H_kv, 128] (this
         layer's new token), q fp16 [B, H_q, 128] -> fp32 [B, H_q, 128]."""
         import torch
-        q = q.contiguous()
+        k, v, q = k.contiguous(), v.contiguous(), q.contiguous()   # named: the copies live until the call has returned
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
         ws = self.workspace() if workspace is None else workspace
-        check(self._lib.semkv_append_decode(self._cref, layer, _ptr(k.contiguous()), _ptr(v.contiguous()),
-                                        _ptr(q), _ptr(out), _ptr(ws), ws.numel() * ws.element_size(), _stream()),
-              "semkv_append_decode")
+        check(self._lib.semkv_append_decode(self._cref, layer, _ptr(k), _ptr(v), _ptr(q), _ptr(out), _ptr(ws),
+                                            ws.numel() * ws.element_size(), _stream()), "semkv_append_decode")
         return out
 
     # -- state -------------------------------------------------------------

@@ -156,3 +156,37 @@ def test_fused_append_decode_matches_separate_calls(wl, base):
                     nt = -(-n // 64)
                     assert torch.equal(sep.pool_bytes(b, l, h, p, nt), fus.pool_bytes(b, l, h, p, nt))
     assert torch.equal(sep.tail.view(-1, 2, 64, 128)[:, :, :sep.c.n_scored], fus.tail.view(-1, 2, 64, 128)[:, :, :fus.c.n_scored])
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_append_takes_rows_that_are_not_contiguous(fused):
+    """A step's K and V as slices of [B, H, n, 128], its query and its score as
+    strided views: the tail, the scores and the attention are those of the
+    contiguous rows, bit for bit."""
+    import torch
+    cfgw = get_config(3, n_layers=1, batch=2, n_kv_heads=2, n_q_heads=8)
+    T, n_gen = 150, 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    K, V = (torch.randn((2, 2, n_gen, 128), generator=g, device="cuda").half() for _ in range(2))
+    q = torch.randn((2, 8, 256), generator=g, device="cuda").half()[:, :, ::2]
+    s = torch.rand((2, n_gen), generator=g, device="cuda")
+    got = []
+    for same in (lambda x: x, lambda x: x.contiguous()):
+        c = U.make_cache(cfgw, T, max_new=n_gen)
+        U.prefill(c, cfgw, T)
+        c.tail.zero_()
+        outs = []
+        for i in range(n_gen):
+            k, v = same(K[:, :, i]), same(V[:, :, i])
+            if fused:
+                outs.append(c.append_decode_attn(0, k, v, same(q)))
+            else:
+                c.append_kv(0, k, v)
+                outs.append(c.decode_attn(0, same(q)))
+            c.append_commit(same(s[:, i]))
+        tail = c.tail.view(2, 1, 2, 2, 64, 128)
+        assert torch.equal(tail[:, 0, :, 0, :n_gen], K) and torch.equal(tail[:, 0, :, 1, :n_gen], V)
+        assert torch.equal(c.tail_scores.view(2, 64)[:, :n_gen], s)
+        got.append(torch.stack(outs))
+    assert torch.equal(got[0], got[1])
