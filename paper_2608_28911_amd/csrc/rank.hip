@@ -401,6 +401,7 @@ __global__ __launch_bounds__(kMT) void rank_final_kernel(RankArgs a) {
   scan256(gb, wsum, &gt_before);
   scan256(eb, wsum, &eq_before);
   chunk_keys<true>(a, c, key, valid, nan);
+  if (!any && nan) atomicOr(a.status, 1);                // no token taken: launch 1 did not look
   uint32_t nt = 0;
 #pragma unroll
   for (int j = 0; j < kMRun; ++j) nt += ((valid >> j) & 1u) && key[j] == theta ? 1u : 0u;

@@ -182,15 +182,20 @@ def test_one_workgroup_ranker_reports_nan():
     assert cache.status() & 1
 
 
-def test_multi_chunk_ranker_reports_nan():
+@pytest.mark.parametrize("r", [(26, 100), (0, 1)])
+def test_multi_chunk_ranker_reports_nan(r):
+    """A NaN in the last, one-token chunk of the second sequence; with K = 0
+    the list is written without the selecting launches."""
     import torch
-    cfgw = get_config(0, batch=1, n_kv_heads=1, n_q_heads=4, n_layers=1)
-    cache = U.make_cache(cfgw, 9000, n_layers=1, max_new=0)
-    s = np.random.default_rng(5).standard_normal((1, 9000)).astype(np.float32)
-    s[0, 8500] = np.nan
+    cfgw = get_config(0, batch=2, n_kv_heads=1, n_q_heads=4, n_layers=1, r_num=r[0], r_den=r[1])
+    T = 5 * 4096 + 1
+    cache = U.make_cache(cfgw, T, n_layers=1, max_new=0)
+    s = np.random.default_rng(5).standard_normal((2, T)).astype(np.float32)
     cache.rank(torch.from_numpy(s).cuda())
-    torch.cuda.synchronize()
-    assert cache.status() & 1
+    assert cache.status() == 0
+    s[1, T - 1] = np.nan
+    cache.rank(torch.from_numpy(s).cuda())
+    assert cache.status() == 1
 
 
 @pytest.mark.parametrize("r", [(0, 1), (1, 1), (1, 2)])
