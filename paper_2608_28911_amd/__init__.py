@@ -99,9 +99,19 @@ class SemKVCache:
                                      _ptr(self.signs) if self.signs is not None else None,
                                      _ptr(self.status_word)), "semkv_cache_init")
         self._ws = None
-        self._cref = ctypes.byref(self.c)
         self._lib = lib()
-        self._cfg = self.c.cfg               # a view: reads the cache's own configuration
+
+    @property
+    def c(self):
+        """The library's view of the cache: configuration, pointers and counts."""
+        return self._c
+
+    @c.setter
+    def c(self, c):
+        # what every call passes is made here, once, and follows the struct
+        self._c = c
+        self._cref = ctypes.byref(c)
+        self._cfg = c.cfg                    # a view: reads the struct's own configuration
 
     # -- the hot path ------------------------------------------------------
     def rank_sizes(self, T):

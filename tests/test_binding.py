@@ -23,10 +23,11 @@ class Recorder:
     read while the call runs."""
 
     def __init__(self, **sizes):
-        self.sizes, self.seen = sizes, {}
+        self.sizes, self.seen, self.args = sizes, {}, {}
 
     def __getattr__(self, name):
         def call(*args):
+            self.args[name] = args
             self.seen[name] = {i: ctypes.string_at(args[i], n) for i, n in self.sizes[name].items()}
             return 0
         return call
@@ -61,3 +62,18 @@ def test_append_copies_of_rows_live_until_the_call(monkeypatch):
     s = torch.arange(2.0 * B)[::2]
     c.append_commit(s)
     assert lib.seen["semkv_append_commit"] == {1: raw(s)}
+
+
+def test_calls_follow_a_replaced_struct(monkeypatch):
+    """cache.c may be replaced (a saved copy of the counts, say): the library's
+    calls, the counts and the list sizes are then all those of the new struct."""
+    c = make_cache(monkeypatch)
+    new = type(c.c).from_buffer_copy(c.c)
+    new.cfg.r_num, new.n_hi, new.n_lo = 50, 100, 300
+    c.c = new
+    assert c.counts["n_hi"] == 100 and c.rank_sizes(200) == (100, 100)
+    c._lib = lib = Recorder(semkv_rank={})
+    hi, lo = c.rank(torch.zeros((B, 200)))
+    assert hi.shape == (B, 100) and lo.shape == (B, 100)
+    struct = lib.args["semkv_rank"][0]._obj
+    assert ctypes.addressof(struct) == ctypes.addressof(new)
