@@ -48,6 +48,8 @@
 // rotated query H diag(sign) q and accumulate values in the rotated domain.
 #include <hip/hip_fp16.h>
 
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "semkv_internal.h"
@@ -318,8 +320,9 @@ constexpr int kLaneGroup = 16 * 16 + 16;                     // bytes per lane g
 template <int BASE, int L>
 struct PoolConst {
   using Tr = Traits<BASE, L>;
-  uint32_t lut[Tr::LUTDW];
-  uint32_t pvw[64][4];
+  // pvw is read 16 bytes at a time, lut up to 8
+  alignas(16) uint32_t lut[Tr::LUTDW];
+  alignas(16) uint32_t pvw[64][4];
   constexpr PoolConst() : lut(), pvw() {
     for (int e = 0; e < Tr::NENT; ++e) {
       lut[e * Tr::TED] = entry_dword<BASE, L, 0>(uint32_t(e));
@@ -335,6 +338,14 @@ struct PoolConst {
 };
 template <int BASE, int L>
 __device__ const PoolConst<BASE, L> kPoolConst{};
+template <int BASE, int L>
+constexpr bool pool_const_aligned() {
+  using C = PoolConst<BASE, L>;
+  return alignof(C) >= 16 && offsetof(C, lut) % 16 == 0 && offsetof(C, pvw) % 16 == 0 && sizeof(C::pvw[0]) == 16;
+}
+static_assert(pool_const_aligned<0, 2>() && pool_const_aligned<0, 3>() && pool_const_aligned<0, 4>() &&
+              pool_const_aligned<0, 5>() && pool_const_aligned<0, 6>() && pool_const_aligned<0, 7>() &&
+              pool_const_aligned<0, 8>() && pool_const_aligned<1, 3>() && pool_const_aligned<1, 4>(), "vector loads");
 
 // 16-byte piece q of the replicated LDS table (entry e of replica r at entry
 // slot e R + r; R >= 4, so a piece lies in one entry, repeated)
