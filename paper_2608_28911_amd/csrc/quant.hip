@@ -205,6 +205,12 @@ __device__ inline void swap32x4(float& a0, float& b0, float& a1, float& b1, floa
           "v_permlane32_swap_b32 %4, %5\n\tv_permlane32_swap_b32 %6, %7"
           : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1), "+v"(a2), "+v"(b2), "+v"(a3), "+v"(b3));
 }
+__device__ inline void swap16x2(float& a0, float& b0, float& a1, float& b1) {
+  __asm__("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3" : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1));
+}
+__device__ inline void swap32x2(float& a0, float& b0, float& a1, float& b1) {
+  __asm__("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3" : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1));
+}
 // the value of f over the four lanes of a row, in all of them
 template <class F>
 __device__ inline float row_reduce(float v, F f) {
@@ -339,52 +345,101 @@ __device__ uint16_t tq_row(float u[32], const float* tau, uint32_t code[8]) {
   return r16;
 }
 
+// The reductions f and g of a row's NG values of v and of w, one value a group:
+// lane quarter q is left with those of group q % NG (NG = 1: every lane).  The
+// swaps halve the values held as they fold the row, so four groups take 6 swaps
+// (each group folded over the row by itself: 16).
+template <int NG, class F, class E>
+__device__ inline void row_reduce_groups(float (&v)[NG], float (&w)[NG], F f, E g, float& rv, float& rw) {
+  if constexpr (NG == 4) {
+    swap16x4(v[0], v[1], v[2], v[3], w[0], w[1], w[2], w[3]);
+    float a = f(v[0], v[1]), b = f(v[2], v[3]), c = g(w[0], w[1]), d = g(w[2], w[3]);
+    swap32x2(a, b, c, d);
+    rv = f(a, b), rw = g(c, d);
+  } else {
+    float a, c;
+    if constexpr (NG == 2) {
+      swap16x2(v[0], v[1], w[0], w[1]);
+      a = f(v[0], v[1]), c = g(w[0], w[1]);
+    } else {
+      float b = a = v[0], d = c = w[0];
+      swap16x2(a, b, c, d);
+      a = f(a, b), c = g(c, d);
+    }
+    float b = a, d = c;
+    swap32x2(a, b, c, d);
+    rv = f(a, b), rw = g(c, d);
+  }
+}
+// The way back: x and y of group q % NG, held by lane quarter q, in every lane
+// of the row as xs[group] and ys[group].
+template <int NG>
+__device__ inline void row_spread_groups(float x, float y, float (&xs)[NG], float (&ys)[NG]) {
+  if constexpr (NG == 4) {
+    float a = x, b = x, c = y, d = y;
+    swap32x2(a, b, c, d);                    // a, c: of quarters 0 and 1, in both halves; b, d: of 2 and 3
+    xs[0] = xs[1] = a, xs[2] = xs[3] = b;
+    ys[0] = ys[1] = c, ys[2] = ys[3] = d;
+    swap16x4(xs[0], xs[1], xs[2], xs[3], ys[0], ys[1], ys[2], ys[3]);
+  } else if constexpr (NG == 2) {
+    xs[0] = xs[1] = x, ys[0] = ys[1] = y;
+    swap16x2(xs[0], xs[1], ys[0], ys[1]);
+  } else {
+    xs[0] = x, ys[0] = y;
+  }
+}
+
 // Affine quantizer of the rotated row (Sec. 4.1 with its Hadamard rotation):
 // y = H diag(sign) x / 16 (the division is exact), then per group of G
 // rotated coordinates zero = fp16(min y) (-0 stored as +0) and scale =
 // fp16(max(0, (max y - zero) / (L-1))), each saturated at +-65504, codes
-// against the stored pair.  u: H diag(sign) x.  meta[g]: {scale, zero} of
-// group g as fp16 bits (low half = scale).
+// against the stored pair.  u: H diag(sign) x.  Returns {scale, zero} of the
+// lane quarter's group (q % (128 / G)) as fp16 bits (low half = scale).
+// Every lane holds channels of every group, but works out the parameters of
+// one and gets the others' by swaps: two IEEE divisions a row and lane.  With
+// every group's parameters in every lane (eight divisions at G = 32), packing
+// 16 x 4096 tokens of a layer at 6/5 levels took 127 us at G = 32 and 110 at
+// 64, now 100 and 97 (100 at 128).
 template <int L, int G>
-__device__ inline void rot_affine_row(const float u[32], uint32_t meta[128 / G], uint32_t code[8]) {
+__device__ inline uint32_t rot_affine_row(const float u[32], uint32_t code[8]) {
   constexpr int NG = 128 / G;
+  float mn[NG], mx[NG];
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    // registers of the group: 16 q0 + 8 q1 + i, i < 8
-    float mn = INFINITY, mx = -INFINITY;
+  for (int i = 0; i < NG; ++i) mn[i] = INFINITY, mx[i] = -INFINITY;
+  // registers 16 q0 + 8 q1 + i, i < 8, are of group (64 q1 + 32 q0) / G
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const int q0 = i >> 4, q1 = (i >> 3) & 1;
-      if ((64 * q1 + 32 * q0) / G != g) continue;
-      mn = fminf(mn, u[i]);
-      mx = fmaxf(mx, u[i]);
-    }
-    // the exact 1/16 of the extremes; of the values in the code's subtraction
-    mn = row_reduce(mn, [](float p, float r) { return fminf(p, r); }) * 0.0625f;
-    mx = row_reduce(mx, [](float p, float r) { return fmaxf(p, r); }) * 0.0625f;
-    // rotated coordinates reach 128 * 65504 / 16 in magnitude: both parameters
-    // saturate at +-65504
-    uint16_t z16 = sat16(f2h(mn));
-    z16 = z16 == 0x8000u ? uint16_t(0) : z16;
-    const float zero = h2f(z16);
-    const float s32 = __fdiv_rn(mx - zero, float(L - 1));
-    const uint16_t s16 = sat16(f2h(s32 > 0.0f ? s32 : 0.0f));
-    const float sf = h2f(s16);
-    const float inv = sf == 0.0f ? 0.0f : __fdiv_rn(1.0f, sf);
-    meta[g] = uint32_t(s16) | (uint32_t(z16) << 16);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int q0 = k >> 2, q1 = (k >> 1) & 1;
-      if ((64 * q1 + 32 * q0) / G != g) continue;
-      uint32_t w = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {                       // clamp, then round in the convert
-        const float c = fminf(fmaxf(fmaf(u[4 * k + e], 0.0625f, -zero) * inv, 0.0f), float(L - 1));
-        w = __builtin_amdgcn_cvt_pk_u8_f32(c, e, w);
-      }
-      code[k] = w;
-    }
+  for (int i = 0; i < 32; ++i) {
+    const int g = (64 * ((i >> 3) & 1) + 32 * (i >> 4)) / G;
+    mn[g] = fminf(mn[g], u[i]);
+    mx[g] = fmaxf(mx[g], u[i]);
   }
+  float lo, hi;
+  row_reduce_groups<NG>(mn, mx, [](float p, float r) { return fminf(p, r); }, [](float p, float r) { return fmaxf(p, r); }, lo, hi);
+  // the exact 1/16 of the extremes; of the values in the code's subtraction
+  lo *= 0.0625f;
+  hi *= 0.0625f;
+  // rotated coordinates reach 128 * 65504 / 16 in magnitude: both parameters
+  // saturate at +-65504
+  uint16_t z16 = sat16(f2h(lo));
+  z16 = z16 == 0x8000u ? uint16_t(0) : z16;
+  const float z = h2f(z16);
+  const float s32 = __fdiv_rn(hi - z, float(L - 1));
+  const uint16_t s16 = sat16(f2h(s32 > 0.0f ? s32 : 0.0f));
+  const float sf = h2f(s16);
+  float zero[NG], inv[NG];
+  row_spread_groups<NG>(z, sf == 0.0f ? 0.0f : __fdiv_rn(1.0f, sf), zero, inv);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int g = (64 * ((k >> 1) & 1) + 32 * (k >> 2)) / G;
+    uint32_t w = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {                         // clamp, then round in the convert
+      const float c = fminf(fmaxf(fmaf(u[4 * k + e], 0.0625f, -zero[g]) * inv[g], 0.0f), float(L - 1));
+      w = __builtin_amdgcn_cvt_pk_u8_f32(c, e, w);
+    }
+    code[k] = w;
+  }
+  return uint32_t(s16) | (uint32_t(z16) << 16);
 }
 
 // The row and the quarter of it that a thread of the workgroup holds while
@@ -398,8 +453,8 @@ __device__ inline int quarter_of_thread(int tid) { return BASE == 0 ? tid & 3 : 
 // Quantize a row's K or V: every thread of the row writes its codes to the
 // row of the code array (zeros for a row that is not there) and the metadata
 // of its share of the groups.  m: the rotating bases' sign masks.  bad: a value
-// was not finite.
-template <int BASE, int L>
+// was not finite.  GC: the rotated affine base's group size, 0 to read it from g.
+template <int BASE, int L, int GC>
 __device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid, int q, const uint32_t m[16],
                              const float* tau, uint8_t* codes, uint8_t* meta_dst, int slot, bool& bad) {
   if constexpr (BASE == 0) {
@@ -424,15 +479,13 @@ __device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid,
       if (q == 0) reinterpret_cast<uint16_t*>(meta_dst)[slot] = valid ? r : uint16_t(0);
     } else {
       rotate_row(u);
-      auto affine = [&](auto GC) {
-        constexpr int G = decltype(GC)::value;
-        uint32_t w[128 / G];
-        rot_affine_row<L, G>(u, w, code);
-#pragma unroll
-        for (int i = 0; i < 128 / G; ++i)
-          if (q == i) reinterpret_cast<uint32_t*>(meta_dst)[i * kSlots + slot] = valid ? w[i] : 0u;
+      auto affine = [&](auto GI) {
+        constexpr int G = decltype(GI)::value;
+        const uint32_t w = rot_affine_row<L, G>(u, code);
+        if (q < 128 / G) reinterpret_cast<uint32_t*>(meta_dst)[q * kSlots + slot] = valid ? w : 0u;
       };
-      if (g.G == 128) affine(std::integral_constant<int, 128>{});
+      if constexpr (GC != 0) affine(std::integral_constant<int, GC>{});
+      else if (g.G == 128) affine(std::integral_constant<int, 128>{});
       else if (g.G == 64) affine(std::integral_constant<int, 64>{});
       else affine(std::integral_constant<int, 32>{});
     }
@@ -598,7 +651,7 @@ struct Lds {
   alignas(16) uint32_t bv[kMaxBodyWords + 8];
 };
 
-template <int BASE, int L>
+template <int BASE, int L, int GC>
 __device__ void prefill_record(const QuantArgs& a, Lds& s, int pool, int tile, int b, int l, int h) {
   const PoolGeom& g = a.g;
   const int tid = threadIdx.x, r = row_of_thread<BASE>(tid), q = quarter_of_thread<BASE>(tid);
@@ -618,7 +671,7 @@ __device__ void prefill_record(const QuantArgs& a, Lds& s, int pool, int tile, i
   const int64_t base_off = int64_t(l) * a.sL + int64_t(b) * a.sB + int64_t(h) * a.sH + int64_t(tok) * a.sT + 32 * q;
 #pragma unroll
   for (int kv = 0; kv < 2; ++kv)
-    quantize_row<BASE, L>(g, (kv ? a.V : a.K) + base_off, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
+    quantize_row<BASE, L, GC>(g, (kv ? a.V : a.K) + base_off, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
                           rec + 2 * tb + kv * g.meta_bytes, r, bad);
   if (bad && valid) atomicOr(g.status, 2);
   __syncthreads();
@@ -627,14 +680,17 @@ __device__ void prefill_record(const QuantArgs& a, Lds& s, int pool, int tile, i
   store_bodies(rec, s.bk, s.bv, tb);
 }
 
-template <int BASE, int LH, int LL>
+// The rotated affine base has a kernel per group size (GC): with the size read
+// at run time, the branches on it kept V's loads behind K's work, and 3 x 5003
+// tokens of a layer at 6/5 levels and G = 128 took 23.4 us instead of 22.2.
+template <int BASE, int LH, int LL, int GC>
 __global__ __launch_bounds__(256) void quantize_pack_kernel(QuantArgs a) {
   __shared__ Lds s;
   int tile = blockIdx.x, pool = blockIdx.y & 1, h = blockIdx.y >> 1;
   int b = blockIdx.z / a.n_layers_launched, l = a.layer0 + blockIdx.z % a.n_layers_launched;
   if (int64_t(tile) * kSlots >= a.n_pool[pool]) return;
-  if (pool == 0) prefill_record<BASE, LH>(a, s, 0, tile, b, l, h);
-  else prefill_record<BASE, LL>(a, s, 1, tile, b, l, h);
+  if (pool == 0) prefill_record<BASE, LH, GC>(a, s, 0, tile, b, l, h);
+  else prefill_record<BASE, LL, GC>(a, s, 1, tile, b, l, h);
 }
 
 // ---------------------------------------------------------------- close --
@@ -678,7 +734,7 @@ __device__ void close_record(const CloseArgs& a, Lds& s, const int* row_of, int 
     if constexpr (BASE != 0) sign_masks(g.signs[(int64_t(l) * g.n_kv_heads + h) * 4 + q], m);
 #pragma unroll
     for (int kv = 0; kv < 2; ++kv)
-      quantize_row<BASE, L>(g, src + kv * kSlots * kD, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
+      quantize_row<BASE, L, 0>(g, src + kv * kSlots * kD, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
                             rec + 2 * tb + kv * g.meta_bytes, r, bad);
   }
   if (bad && valid) atomicOr(g.status, 2);
@@ -821,7 +877,16 @@ __global__ void append_kernel(AppendArgs a) {
 template <int BASE, int LH, int LL>
 int launch_qp(const QuantArgs& a, hipStream_t st) {
   dim3 grid(a.max_tiles, 2 * a.g.n_kv_heads, a.g.batch * a.n_layers_launched);
-  hipLaunchKernelGGL((quantize_pack_kernel<BASE, LH, LL>), grid, dim3(256), 0, st, a);
+  if constexpr (BASE != 2) {
+    hipLaunchKernelGGL((quantize_pack_kernel<BASE, LH, LL, 0>), grid, dim3(256), 0, st, a);
+  } else {
+    // metadata finer than a row only at 6/5 and 5/4 levels
+    constexpr bool FINE = LH == LL + 1 && (LL == 5 || LL == 4);
+    if (a.g.G == 128) hipLaunchKernelGGL((quantize_pack_kernel<BASE, LH, LL, 128>), grid, dim3(256), 0, st, a);
+    else if (FINE && a.g.G == 64) hipLaunchKernelGGL((quantize_pack_kernel<BASE, LH, LL, FINE ? 64 : 128>), grid, dim3(256), 0, st, a);
+    else if (FINE && a.g.G == 32) hipLaunchKernelGGL((quantize_pack_kernel<BASE, LH, LL, FINE ? 32 : 128>), grid, dim3(256), 0, st, a);
+    else return -2;
+  }
   return hipGetLastError() == hipSuccess ? 0 : -5;
 }
 

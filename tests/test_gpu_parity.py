@@ -255,6 +255,49 @@ def test_rotated_affine_base(levels, G):
     _check_decode(cache, cfgw, 1000, flags, [0, 1])
 
 
+@pytest.mark.parametrize("G", [32, 64, 128])
+@pytest.mark.parametrize("levels", [(6, 5), (5, 4)])
+def test_rotated_affine_groups_of_unlike_range(levels, G):
+    """Rows whose rotated coordinates have a range of their own in each group of
+    32 (from 0.01 to 60, around its own centre, in another order from row to
+    row): a parameter taken from another group shows in the record.  Full and
+    partial records, prompt and closed block."""
+    import torch
+    cfgw = get_config(0, base="rot_affine", L_hi=levels[0], L_lo=levels[1], group=G, batch=1, n_kv_heads=1, n_q_heads=4)
+    T, n_gen = 150, 64
+    rng = np.random.default_rng(G)
+    H = np.array([[1.0]])
+    while len(H) < 128:
+        H = np.block([[H, H], [H, -H]])
+    words = synth.sign_words(cfgw, 0, 0)
+    sign = 1.0 - 2.0 * ((words[np.arange(128) // 32] >> (np.arange(128) % 32).astype(np.uint32)) & 1)
+
+    def rows(n):
+        y = rng.standard_normal((n, 4, 32))
+        for t in range(n):
+            k = rng.permutation(4)
+            y[t] = y[t] * np.array([0.01, 0.5, 5.0, 60.0])[k][:, None] + np.array([20.0, -1.0, 0.0, 3.0])[k][:, None]
+        return (sign * (16 * y.reshape(n, 128) @ H / 128)).astype(np.float16)[None, None]
+    K, V, k1, v1 = rows(T), rows(T), rows(n_gen), rows(n_gen)
+    cache = U.make_cache(cfgw, T, n_layers=1, max_new=n_gen)
+    scores, hi, lo = U.prefill(cache, cfgw, T, kv=lambda l: (K, V))
+    f, _, _ = O.rank(scores[0], cfgw.r_num, cfgw.r_den)
+    u = U.oracle_unit(cfgw, 0, 0, 0, f, T, kv=lambda l: (K, V))
+
+    def check():
+        for p in (0, 1):
+            assert np.array_equal(U.gpu_records(cache, 0, 0, 0, p, u.count(p)), u.records(p)), "pool %d" % p
+    check()
+    gs = rng.integers(0, 9, n_gen).astype(np.float32)
+    for i in range(n_gen):
+        cache.append_kv(0, torch.from_numpy(k1[:, :, i].copy()).cuda(), torch.from_numpy(v1[:, :, i].copy()).cuda())
+        cache.append_commit(torch.from_numpy(gs[i:i + 1]).cuda())
+        u.append_kv(k1[0, 0, i], v1[0, 0, i])
+        u.commit(gs[i])
+    assert cache.status() == 0 and cache.counts["n_scored"] == 0
+    check()
+
+
 @pytest.mark.parametrize("T", [1, 65])
 def test_rotated_affine_ragged(T):
     cfgw = get_config(0, base="rot_affine", group=64, n_kv_heads=2, n_q_heads=8)
