@@ -6,10 +6,11 @@
 // holds token 1024 j + t.  A 4-pass 8-bit radix select finds the K-th largest
 // key theta and how many of the keys equal to it are taken (equal keys are
 // taken by increasing token index).  Importance scores are heavily tied
-// (integer Zipf draws, peaked accumulated-attention weights), so a wave adds
-// the bin of its first counted key with a single atomic.  Every pass has a
-// histogram of its own and every wave selects the bin itself, so a pass costs
-// one barrier.  Ballots then give each wave's keys above and equal to theta;
+// (integer Zipf draws, peaked accumulated-attention weights): up to 4096 tokens
+// a wave adds the bin of its first counted key with a single atomic, longer
+// sequences add every key to one of eight copies of the histogram (kReplicas).
+// Every pass has a histogram of its own and every wave selects the bin itself,
+// so a pass costs one barrier.  Ballots then give each wave's keys above and equal to theta;
 // one scan over the (round, wave) counts, and a lane's count of the lower
 // lanes, give every token its slot: a token's place in the high list is the
 // keys above theta before it and the taken ones equal to theta before it.
@@ -75,11 +76,25 @@ __device__ inline void hist_add(uint32_t* hist, uint32_t bin, bool in) {
   }
 }
 
+// Copies of a pass's histogram in the one-workgroup kernel with R keys a thread.
+// A workgroup has one compute unit, which is bound by instructions when every
+// key is counted in every pass: finding a wave's most common bin takes about 25
+// a key and pass, a plain addition 5, and lanes that share a bin wait for each
+// other only within a copy.  Clearing and reading eight copies takes 0.9 us, so
+// short sequences keep one.  Microseconds a call in a graph, one copy / eight,
+// for scores drawn from Zipf, all equal, of two values, and the integers 0..3:
+// 4.4 / 5.3, 4.4 / 5.3, 4.4 / 5.2, 4.4 / 5.3 at 256 tokens; 5.7 / 5.8,
+// 5.9 / 5.9, 6.5 / 5.9, 6.5 / 6.0 at 2048; 9.2 / 8.2, 10.2 / 9.0, 12.0 / 9.1,
+// 12.2 / 8.7 at 6000; 18.0 / 14.4, 20.8 / 17.1, 25.8 / 17.5, 26.4 / 16.3 at
+// 16384, where a workgroup per chunk takes 22.7, 24.5, 25.1 and 24.5.
+constexpr int replicas_of(int R) { return R > 4 ? 8 : 1; }
+
 // one workgroup per sequence of up to 1024 R tokens, R keys per thread
 template <int R>
 __global__ __launch_bounds__(kThreads) void rank_kernel(RankArgs a) {
   constexpr int NE = R * kWaves, PER = (NE + 63) / 64;       // (round, wave) counts, and of them per lane of the scan
-  __shared__ alignas(16) uint32_t hist[4][256];
+  constexpr int REP = replicas_of(R), HS = REP > 1 ? 256 + 64 / REP : 256;   // a bin's copies in different banks
+  __shared__ alignas(16) uint32_t hist[4][REP][HS];
   __shared__ uint32_t cnt[PER * 64];                         // keys above theta << 16 | keys equal to it
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int T = int(a.T);
@@ -90,7 +105,13 @@ __global__ __launch_bounds__(kThreads) void rank_kernel(RankArgs a) {
   uint32_t key[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) key[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (j * kThreads + tid) * 4, 0, 0);
-  (&hist[0][0])[tid] = 0u;
+  if constexpr (REP == 1) {
+    static_assert(sizeof(hist) == 4 * kThreads, "a word a thread");
+    (&hist[0][0][0])[tid] = 0u;
+  } else {
+    static_assert(sizeof(hist) % 16 == 0 && HS % 4 == 0, "histogram pieces");
+    for (int i = tid; i < int(sizeof(hist) / 16); i += kThreads) reinterpret_cast<uint4*>(&hist[0][0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
   bool nan = false;
 #pragma unroll
   for (int j = 0; j < R; ++j) {
@@ -105,15 +126,23 @@ __global__ __launch_bounds__(kThreads) void rank_kernel(RankArgs a) {
   if (K > 0) {
 #pragma unroll
     for (int d = 3; d >= 0; --d) {
-      uint32_t* H = hist[3 - d];
+      uint32_t* H = hist[3 - d][lane & (REP - 1)];
 #pragma unroll
       for (int j = 0; j < R; ++j)
-        if (j * kThreads + wave * 64 < T)                    // the same for the whole wave
-          hist_add(H, (key[j] >> (8 * d)) & 255u,
-                   j * kThreads + tid < T && (d == 3 || (key[j] >> (8 * d + 8)) == (theta >> (8 * d + 8))));
+        if (j * kThreads + wave * 64 < T) {                  // the same for the whole wave
+          const uint32_t k = key[j] >> (8 * d);
+          const bool in = j * kThreads + tid < T && (d == 3 || (k >> 8) == (theta >> (8 * d + 8)));
+          if constexpr (REP == 1) hist_add(H, k & 255u, in);
+          else if (in) atomicAdd(&H[k & 255u], 1u);
+        }
       __syncthreads();
       // lane l takes bins 255 - 4 l .. 252 - 4 l (descending key order)
-      const uint4 q = *reinterpret_cast<const uint4*>(H + 252 - 4 * lane);
+      uint4 q = *reinterpret_cast<const uint4*>(&hist[3 - d][0][252 - 4 * lane]);
+#pragma unroll
+      for (int i = 1; i < REP; ++i) {
+        const uint4 x = *reinterpret_cast<const uint4*>(&hist[3 - d][i][252 - 4 * lane]);
+        q.x += x.x, q.y += x.y, q.z += x.z, q.w += x.w;
+      }
       const uint32_t c[4] = {q.w, q.z, q.y, q.x}, sum = q.x + q.y + q.z + q.w;
       uint32_t above = wave_scan(sum) - sum;                 // keys in the bins of lower lanes
       const uint64_t has = __ballot(above < krem && above + sum >= krem);
@@ -184,10 +213,9 @@ __global__ __launch_bounds__(kThreads) void rank_kernel(RankArgs a) {
 
 // ------------------------------------------- one workgroup per chunk ----
 
-// Longest sequence of the one-workgroup kernel.  Back to back, microseconds a
-// call, one workgroup / one per chunk: 9.0 / 22 at 4096 tokens, 10.6 / 23 at
-// 8192, 14 / 23 at 10007, 18-20 / 24 at 16384, 29-33 / 24 at 24576.  (The
-// kernel before it, which read the scores again in each pass: 15.8 at 4096.)
+// Longest sequence of the one-workgroup kernel.  Scores drawn from Zipf, in a
+// graph, microseconds a call, one workgroup / one per chunk: 9.0 / 22 at 8192
+// tokens, 12.1 / 22 at 10007, 14.4 / 22.6 at 16384.
 constexpr int64_t kRankWG = 16 * kThreads;
 
 constexpr int kMT = 256;                     // threads of a chunk's workgroup
