@@ -101,8 +101,8 @@ typedef struct semkv_config {
  *  tail_scores: fp32 [batch][64].
  *  flags:  uint32 [batch][flag_words]: bit i%32 of word i/32 is 1 iff token i
  *          has the high precision (the 1-bit per-token flag of Sec. 4.1);
- *          then (from word batch*flag_words rounded up to a multiple of 64)
- *          the ranker's scratch for prompts longer than 16384 tokens, per
+ *          then, when max_prompt is above 16384 (from word batch*flag_words
+ *          rounded up to a multiple of 64), the ranker's scratch, per
  *          sequence three histograms of 2048, 2048 and 1024 words, which are
  *          zero again when each semkv_rank call ends, 16 words of selection
  *          state and two counts per 4096-token chunk.  flag_bytes covers both.

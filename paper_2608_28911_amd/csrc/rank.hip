@@ -213,11 +213,6 @@ __global__ __launch_bounds__(kThreads) void rank_kernel(RankArgs a) {
 
 // ------------------------------------------- one workgroup per chunk ----
 
-// Longest sequence of the one-workgroup kernel.  Scores drawn from Zipf, in a
-// graph, microseconds a call, one workgroup / one per chunk: 9.0 / 22 at 8192
-// tokens, 12.1 / 22 at 10007, 14.4 / 22.6 at 16384.
-constexpr int64_t kRankWG = 16 * kThreads;
-
 constexpr int kMT = 256;                     // threads of a chunk's workgroup
 constexpr int kMW = kMT / 64;
 constexpr int kMRun = kRankChunk / kMT;      // 16 tokens per thread
@@ -465,6 +460,8 @@ __global__ __launch_bounds__(kMT) void rank_final_kernel(RankArgs a) {
 }
 
 }  // namespace
+
+static_assert(kRankWG == 16 * kThreads, "the one-workgroup kernel's longest sequence");
 
 int launch_rank(const RankArgs& a, int batch, hipStream_t s) {
   if (a.T <= kRankWG) {

@@ -114,15 +114,20 @@ constexpr int kMaxSplits = 256;   // splits per (sequence, kv head)
 // buffer descriptor word 3 of a raw buffer of 32-bit elements (gfx9 family)
 constexpr int kBufferWord3 = 0x00020000;
 
-// Ranker scratch, per sequence, after the flag bitmaps in the flags buffer
-// (zero at cache init and again after every semkv_rank call): three
-// histograms (2048, 2048 and 1024 bins), 16 words of selection state, then
-// two counts per chunk of kRankChunk tokens.
+// Longest sequence that one workgroup ranks.  Scores drawn from Zipf, in a
+// graph, microseconds a call, one workgroup / one per chunk: 9.0 / 22 at 8192
+// tokens, 12.1 / 22 at 10007, 14.4 / 22.6 at 16384.
+constexpr int64_t kRankWG = 16384;
+
+// Ranker scratch of a cache whose prompts may be longer, per sequence, after
+// the flag bitmaps in the flags buffer (zero at cache init and again after
+// every semkv_rank call): three histograms (2048, 2048 and 1024 bins), 16 words
+// of selection state, then two counts per chunk of kRankChunk tokens.
 constexpr int kRankChunk = 4096;
 constexpr int kRankH1 = 0, kRankH2 = 2048, kRankH3 = 4096, kRankState = 5120, kRankCounts = 5136;
 __host__ __device__ constexpr int64_t rank_chunks(int64_t T) { return (T + kRankChunk - 1) / kRankChunk; }
 __host__ __device__ constexpr int64_t rank_scratch_words(int64_t max_prompt) {
-  return (kRankCounts + 2 * rank_chunks(max_prompt) + 63) / 64 * 64;
+  return max_prompt <= kRankWG ? 0 : (kRankCounts + 2 * rank_chunks(max_prompt) + 63) / 64 * 64;
 }
 __host__ __device__ constexpr int64_t rank_scratch_offset(int64_t batch, int64_t flag_words) {
   return (batch * flag_words + 63) / 64 * 64;

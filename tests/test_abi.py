@@ -70,6 +70,18 @@ def test_sizes_match_the_format(abi):
         assert s.pool_bytes == 2 * 8 * s.unit_stride
 
 
+@pytest.mark.parametrize("max_prompt", [0, 1, 2048, 16384, 16385, 40000])
+def test_flags_hold_scratch_only_for_prompts_that_use_it(abi, max_prompt):
+    """The flag bitmaps, then the long prompts' ranking scratch: none where the
+    longest prompt is ranked by one workgroup (16384 tokens)."""
+    from paper_2608_28911_amd import cache_sizes
+    s = cache_sizes(cfg_for(abi, batch=3, max_prompt=max_prompt))
+    assert s.flag_words == -(-(max_prompt + 128) // 32) + 1
+    bitmaps = -(-3 * s.flag_words // 64) * 64
+    scratch = 0 if max_prompt <= 16384 else -(-(5136 + 2 * -(-max_prompt // 4096)) // 64) * 64
+    assert s.flag_bytes == 4 * (bitmaps + 3 * scratch)
+
+
 @pytest.mark.parametrize("bad,status", [
     (dict(head_dim=64), -2), (dict(n_q_heads=16), -2), (dict(block=32), -2), (dict(L_hi=7), -2),
     (dict(base=1, L_hi=6, L_lo=5), -2), (dict(base=1, L_hi=4, L_lo=3, group=32), -2), (dict(group=16), -2),
