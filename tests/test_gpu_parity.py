@@ -123,15 +123,17 @@ def _multi_chunk_scores(T, seed):
 
 @pytest.mark.parametrize("r", [(0, 1), (1, 2), (26, 100), (1, 1)])
 def test_multi_chunk_ranker(r):
-    """Sequences longer than a 4096-token chunk are ranked by one workgroup
-    per chunk over five launches (histograms in scratch after the flag
-    bitmaps, cleared again by each call).  Two calls in a row on one cache,
-    the second shorter, so the second starts from the scratch the first left:
-    flags and slot lists bit-exact against the oracle for both."""
+    """Sequences longer than 16384 tokens are ranked by one workgroup per
+    4096-token chunk over five launches (histograms in scratch after the flag
+    bitmaps, cleared again by each call).  Calls in a row on one cache, so each
+    long one starts from the scratch the one before left -- shorter, with a last
+    chunk of one token, after a short sequence that takes the one-workgroup
+    kernel, longer again, and the same length with other scores: flags and slot
+    lists bit-exact against the oracle for all."""
     import torch
     cfgw = get_config(0, batch=3, n_kv_heads=1, n_q_heads=4, n_layers=1, r_num=r[0], r_den=r[1])
     cache = U.make_cache(cfgw, 40000, n_layers=1, max_new=0)
-    for T, seed in ((40000, 1), (8193, 2), (4097, 3), (12288, 4)):
+    for T, seed in ((40000, 1), (20481, 2), (16385, 3), (9000, 4), (24576, 5), (24576, 6)):
         s = _multi_chunk_scores(T, seed)
         hi, lo = cache.rank(torch.from_numpy(s).cuda())
         torch.cuda.synchronize()
