@@ -185,28 +185,6 @@ static_assert(digit_slot_inverts<0, 6>() && digit_slot_inverts<0, 5>() && digit_
               digit_slot_inverts<0, 3>() && digit_slot_inverts<1, 4>() && digit_slot_inverts<1, 3>() &&
               digit_slot_inverts<0, 2>() && digit_slot_inverts<0, 7>() && digit_slot_inverts<0, 8>(), "slots");
 
-// floor(s / L^i) for every symbol s < L^n as (s*2^8 * M) >> 32 with
-// M = ceil(2^24 / L^i): one 24-bit high multiply.
-__host__ __device__ constexpr uint32_t magic(int L, int i) {
-  uint64_t p = 1;
-  for (int k = 0; k < i; ++k) p *= uint64_t(L);
-  return uint32_t(((uint64_t(1) << 24) + p - 1) / p);
-}
-
-__host__ __device__ constexpr bool magic_exact(int L) {
-  int n = sym_digits(L);
-  uint64_t top = 1;
-  for (int k = 0; k < n; ++k) top *= uint64_t(L);
-  for (int i = 1; i < n; ++i) {
-    uint64_t p = 1;
-    for (int k = 0; k < i; ++k) p *= uint64_t(L);
-    for (uint64_t s = 0; s < top; ++s)
-      if (((s << 8) * magic(L, i)) >> 32 != s / p) return false;
-  }
-  return true;
-}
-static_assert(magic_exact(6), "digit extraction");
-
 __device__ inline uint32_t mulhi24(uint32_t a, uint32_t b) {
   return uint32_t((uint64_t(a & 0xFFFFFFu) * uint64_t(b & 0xFFFFFFu)) >> 32);
 }
@@ -217,17 +195,6 @@ __device__ inline uint32_t mad_i24(uint32_t a, int b, uint32_t c) {
   uint32_t r;
   __asm__("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
   return r;
-}
-
-// bits [OFF, OFF+W) of a normalized segment
-template <int OFF, int W, int NW>
-__device__ inline uint32_t field(const uint32_t (&seg)[NW]) {
-  constexpr int w = OFF / 32, sh = OFF % 32;
-  if constexpr (sh + W <= 32) {
-    return (seg[w] >> sh) & ((1u << W) - 1u);
-  } else {
-    return __builtin_amdgcn_alignbit(seg[w + 1], seg[w], sh) & ((1u << W) - 1u);
-  }
 }
 
 // ------------------------------------------------------ decode tables ----
@@ -684,9 +651,10 @@ struct Plan {
     return nw * (MSTAGE + PV + 256) + (Traits<BASE, LH>::LUTDW * rh + Traits<BASE, LL>::LUTDW * rl) * 4 +
            (GH::NPAIR + GL::NPAIR) * 64 * 16 + 4 * kD * 4 + 2080 + 3104 + 640;
   }
-  // 8 waves: 2 per SIMD, one workgroup per compute unit.  A level pair whose
-  // 8-wave workgroup does not fit is refused by the host.
-  static constexpr int NW = lds_bytes(8, 4, 4) <= 160 * 1024 ? 8 : 4;
+  // 2 waves per SIMD, one workgroup per compute unit, one thread per (head,
+  // channel) of the query and the output: every level pair fits
+  static constexpr int NW = kDecodeWaves;
+  static_assert(NW * 64 == 4 * kD && lds_bytes(NW, 4, 4) <= 160 * 1024, "workgroup");
   static constexpr int NT = 64 * NW;
   // table replicas per pool: the most that fit, the low pool (the larger
   // share of the tokens) first (32 dword replicas: a conflict-free lookup of
@@ -959,7 +927,19 @@ struct Scale {
         wP{BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[3] - mu[2]), BASE != 1 ? 1.0f : (L == 3 ? 1.0f : mu[2] + mu[3])} {}
 };
 
-// Score A operands of one pool, by the threads that hold the query x (affine)
+// the three bytes of channel c's integer, plane pl, to their places in one pool's operands
+template <int BASE, int L, int G, int POOL, class PL>
+__device__ inline void scatter_bytes(Shared<PL>& sm, int qi, int h, int c, int pl) {
+  using Tr = Traits<BASE, L>;
+  using Ge = Geo<BASE, L, G>;
+  const int p = c / Tr::n, d = c - p * Tr::n, kg = p & 3, sk = p >> 2;
+  uint8_t* dst = reinterpret_cast<uint8_t*>(&sm.aq[(POOL ? PL::GH::NPAIR : 0) + Ge::pair_at(c)][kg * 16 + 4 * h]) +
+                 (sk % Tr::SPC) * Tr::STRIDE + digit_slot<BASE, L>(d) + pl;
+  dst[0] = uint8_t(qi >> 14);
+  dst[16] = uint8_t((qi >> 7) & 0x7F);
+  dst[32] = uint8_t(qi & 0x7F);
+}
+// Score A operands of both pools, by the threads that hold the query x (affine)
 // or the rotated query (bases 1, 2), one per (head h, channel c).  Lane (row m
 // = 4h + s, kg), (group, chunk) pair, slot holds byte s of qi = rint(x 2^e)
 // (tq: of the plane-weighted x) at the channel the slot addresses, |qi| <
@@ -972,17 +952,6 @@ struct Scale {
 // 2.1 us of a 12.1 us launch (the scatter: 0.75), at G = 128 0.75 us (0.45).
 // The group's first thread also leaves the score scale 2^-e and the
 // zero-point term (the sum of q) of its head and group.
-template <int BASE, int L, int G, int POOL, class PL>
-__device__ inline void scatter_bytes(Shared<PL>& sm, int qi, int h, int c, int pl) {
-  using Tr = Traits<BASE, L>;
-  using Ge = Geo<BASE, L, G>;
-  const int p = c / Tr::n, d = c - p * Tr::n, kg = p & 3, sk = p >> 2;
-  uint8_t* dst = reinterpret_cast<uint8_t*>(&sm.aq[(POOL ? PL::GH::NPAIR : 0) + Ge::pair_at(c)][kg * 16 + 4 * h]) +
-                 (sk % Tr::SPC) * Tr::STRIDE + digit_slot<BASE, L>(d) + pl;
-  dst[0] = uint8_t(qi >> 14);
-  dst[16] = uint8_t((qi >> 7) & 0x7F);
-  dst[32] = uint8_t(qi & 0x7F);
-}
 template <int BASE, int LH, int LL, int G, class PL>
 __device__ inline void scatter_query(const DecodeArgs& a, Shared<PL>& sm, float x, int h, int c) {
   constexpr int GQ = PL::GH::GQ;
@@ -1039,9 +1008,8 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
     const uint4 v = sm.aq[A0 + pair][lane];
     return __builtin_bit_cast(int4v, uint4v{v.x, v.y, v.z, v.w});
   };
-  constexpr bool AREG = NG == 1;
-  int4v Aq[AREG ? Tr::NCK : 1];
-  if constexpr (AREG) {
+  int4v Aq[NG == 1 ? Tr::NCK : 1];
+  if constexpr (NG == 1) {
 #pragma unroll
     for (int c = 0; c < Tr::NCK; ++c) Aq[c] = aq(c);
   }
@@ -1174,7 +1142,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
       chunk_operands<BASE, L, S, VFULL, Tr::VSEGW, Tr::NSV, Tr::NCV>(seg, vmask, lut, B);
     };
     k_operands(0, Bk[0]);
-    constexpr bool DEFER = NG == 1;          // score arithmetic after the value segment reads
+    constexpr bool DEFER = NG == 1;          // score arithmetic after the first value segment's table reads are issued
     int4v acck[DEFER ? 4 : 1][NG];
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
@@ -1190,7 +1158,7 @@ __device__ void run_pool(const DecodeArgs& a, Shared<PL>& sm, WaveState<PL::NGV>
           if constexpr (Ge::pair_used(i, ch)) {              // else chunk ch holds no channel of group i
             int4v A;
             constexpr int pair = Ge::pair_of(i, ch);
-            if constexpr (AREG) A = Aq[ch];
+            if constexpr (NG == 1) A = Aq[ch];
             else A = aq(pair);
             acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, Bk[blk & 1][ch], acc[i], 0, 0, 0);
           }
@@ -1367,7 +1335,7 @@ __device__ inline void st_agent(float* p, float v) {
 
 
 // The unnormalized Walsh-Hadamard transform H x of the 4 rows of 128 values
-// held one per thread by threads 0..511 (thread t: row t >> 7, entry t & 127).
+// held one per thread of the workgroup (thread t: row t >> 7, entry t & 127).
 // Stages 1..32 pair lanes of one wave (DPP quad permutes for 1 and 2, lane
 // exchanges for the rest); stage 64 pairs the two waves of a row through the
 // LDS buffer xch.  Each stage computes the lower entry as lower + upper and the
@@ -1384,13 +1352,10 @@ __device__ inline float fwht_rows(float x, float (*xch)[kD]) {
     p = __shfl_xor(x, hs);
     x = (lane & hs) ? p - x : x + p;
   }
-  const bool mine = tid < 4 * kD;
-  if (mine) xch[tid >> 7][tid & 127] = x;
+  xch[tid >> 7][tid & 127] = x;
   __syncthreads();
-  if (mine) {
-    p = xch[tid >> 7][(tid & 127) ^ 64];
-    x = (tid & 64) ? p - x : x + p;
-  }
+  p = xch[tid >> 7][(tid & 127) ^ 64];
+  x = (tid & 64) ? p - x : x + p;
   __syncthreads();
   return x;
 }
@@ -1522,17 +1487,16 @@ __device__ void merge_splits(const DecodeArgs& a, Shared<PL>& sm, int vb, int la
   // thread (head h, quarter q, channel quad cq) takes the splits s = q, q+4,
   // ... with 16-byte loads at the coherent level (cache policy sc1, as the
   // agent-scope loads), then the four quarters merge in LDS
-  const bool mine = tid < 4 * kD;
-  const int h = (tid >> 7) & 3, q = (tid >> 5) & 3, cq = tid & 31;
+  const int h = tid >> 7, q = (tid >> 5) & 3, cq = tid & 31;
   // the sign of this thread's output channel (rotated bases), loaded first
-  const uint32_t sbits = BASE != 0 && mine ? a.g.signs[(int64_t(layer) * a.g.n_kv_heads + kvh) * 4 + ((tid & 127) >> 5)] : 0u;
+  const uint32_t sbits = BASE != 0 ? a.g.signs[(int64_t(layer) * a.g.n_kv_heads + kvh) * 4 + ((tid & 127) >> 5)] : 0u;
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(unit), 0, ns * 4 * kPartial * 4, kBufferWord3);
   constexpr int kCoherent = 16;              // sc1
   constexpr int kBatch = 8;
   float M = -INFINITY, Lsum = 0.0f;
   float4v o = float4v{0, 0, 0, 0};
-  for (int s0 = q; mine && s0 < ns; s0 += 4 * kBatch) {
+  for (int s0 = q; s0 < ns; s0 += 4 * kBatch) {
     float mv[kBatch], lv[kBatch];
     float4v x[kBatch];
     // all loads issued at once, unconditionally (one round trip): a split
@@ -1566,34 +1530,29 @@ __device__ void merge_splits(const DecodeArgs& a, Shared<PL>& sm, int vb, int la
   struct Quarters { float m[4][4], l[4][4]; float4v o[4][4][32]; };
   static_assert(sizeof(Quarters) <= sizeof(sm.pv), "merge scratch");
   Quarters& qs = *reinterpret_cast<Quarters*>(&sm.pv[0][0]);
-  if (mine) {
-    if (cq == 0) {
-      qs.m[h][q] = M;
-      qs.l[h][q] = Lsum;
-    }
-    qs.o[h][q][cq] = o;
+  if (cq == 0) {
+    qs.m[h][q] = M;
+    qs.l[h][q] = Lsum;
   }
+  qs.o[h][q][cq] = o;
   __syncthreads();
-  const int hc = tid >> 7, c = tid & 127;
-  float r = 0.0f;
-  if (mine) {
-    float Mx = -INFINITY;
+  const int c = tid & 127;
+  float Mx = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) Mx = fmaxf(Mx, qs.m[hc][k]);
-    float L = 0.0f, O = 0.0f;
+  for (int k = 0; k < 4; ++k) Mx = fmaxf(Mx, qs.m[h][k]);
+  float L = 0.0f, O = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float sc = qs.m[hc][k] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(qs.m[hc][k] - Mx);
-      L += qs.l[hc][k] * sc;
-      O += qs.o[hc][k][c >> 2][c & 3] * sc;
-    }
-    r = O / L;
+  for (int k = 0; k < 4; ++k) {
+    const float sc = qs.m[h][k] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(qs.m[h][k] - Mx);
+    L += qs.l[h][k] * sc;
+    O += qs.o[h][k][c >> 2][c & 3] * sc;
   }
+  float r = O / L;
   if (BASE != 0) {
     r = fwht_rows(r, sm.ts.o);
     r = ((sbits >> (c & 31)) & 1u) ? -r : r;
   }
-  if (mine) a.out[((int64_t(vb) * a.g.n_kv_heads + kvh) * 4 + hc) * kD + c] = r;
+  a.out[((int64_t(vb) * a.g.n_kv_heads + kvh) * 4 + h) * kD + c] = r;
 }
 
 template <int BASE, int LH, int LL, int G>
@@ -1602,7 +1561,6 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   constexpr int NW = PL::NW, NT = PL::NT;
   __shared__ Shared<PL> sm;
   static_assert(sizeof(Shared<PL>) <= 160 * 1024, "LDS");
-  static_assert(NT >= 4 * kD, "one thread per (head, channel) of the query and the output");
   // blockIdx.z = (layer of the launch) x batch + sequence: an all-layers
   // launch covers n_layers_launched layers from a.layer
   const int split = blockIdx.x, kvh = blockIdx.y, vb = blockIdx.z;
@@ -1611,14 +1569,12 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
   const PoolGeom& g = a.g;
   SEMKV_STAMP(0);
 
-  // ---- the query first (the longest wait of the prologue); its work takes
-  // the first 4 x 128 threads, one per (head, channel) -- with 8 waves every
-  // thread, known at compile time, so no branch forces a wait on the load
-  const bool qt = NT == 4 * kD || tid < 4 * kD;
-  const int h = qt ? tid >> 7 : 0, c = tid & 127;
-  const uint16_t qbits = qt ? a.q[((int64_t(vb) * g.n_kv_heads * 4) + kvh * 4 + h) * kD + c] : uint16_t(0);
+  // ---- the query first (the longest wait of the prologue), one (head,
+  // channel) per thread, so no branch forces a wait on the load
+  const int h = tid >> 7, c = tid & 127;
+  const uint16_t qbits = a.q[((int64_t(vb) * g.n_kv_heads * 4) + kvh * 4 + h) * kD + c];
   // rotated bases: the sign word of this thread's channel, in flight with the query
-  const uint32_t qsign = BASE != 0 && qt ? g.signs[(int64_t(layer) * g.n_kv_heads + kvh) * 4 + (c >> 5)] : 0u;
+  const uint32_t qsign = BASE != 0 ? g.signs[(int64_t(layer) * g.n_kv_heads + kvh) * 4 + (c >> 5)] : 0u;
 
   // ---- fused append (Alg. 2): the workgroup that attends over the fp16 tail
   // first stores this layer's new K/V row in it, as its last row (read back
@@ -1675,20 +1631,15 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
       if (tid + k * NT < PL::LUTL / 4) d[PL::LUTH / 4 + tid + k * NT] = tl[k];
   }
   SEMKV_STAMP_FINE(19);
-  float xq = 0.0f;
-  if (qt) {
-    xq = hf(qbits);
-    sm.qorig[h][c] = xq;
-    if (BASE != 0) xq = ((qsign >> (c & 31)) & 1u) ? -xq : xq;
-  }
+  float xq = hf(qbits);
+  sm.qorig[h][c] = xq;
+  if (BASE != 0) xq = ((qsign >> (c & 31)) & 1u) ? -xq : xq;
   SEMKV_STAMP_FINE(20);
   if (BASE != 0) xq = fwht_rows(xq, sm.ts.o);    // rotate: H (sign . q)
-  if (qt) {
-    query_runs(xq, h, c, sm);                   // the query the scores use: its runs
-  }
+  query_runs(xq, h, c, sm);                      // the query the scores use: its runs
   SEMKV_STAMP_FINE(21);
   __syncthreads();
-  if (qt) scatter_query<BASE, LH, LL, G>(a, sm, xq, h, c);
+  scatter_query<BASE, LH, LL, G>(a, sm, xq, h, c);
   __syncthreads();
   SEMKV_STAMP(1);
 
@@ -1722,31 +1673,29 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
 
   // ---- workgroup partial: merge of the waves' (and the tail's) states
   SEMKV_STAMP(10);
-  if (qt) {
-    float M = -INFINITY;
+  float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, wave_fin(sm, w)->m[h]);
-    if (tail) M = fmaxf(M, sm.tfin.m[h]);
-    float Lsum = 0.0f, o = 0.0f;
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, wave_fin(sm, w)->m[h]);
+  if (tail) M = fmaxf(M, sm.tfin.m[h]);
+  float Lsum = 0.0f, o = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const Fin* f = wave_fin(sm, w);
-      const float sc = f->m[h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(f->m[h] - M);
-      Lsum += f->l[h] * sc;
-      o += f->o[h][c] * sc;
-    }
-    if (tail) {
-      const float sc = sm.tfin.m[h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(sm.tfin.m[h] - M);
-      Lsum += sm.tfin.l[h] * sc;
-      o += sm.tfin.o[h][c] * sc;
-    }
-    float* dst = a.ws + ((int64_t(vb) * g.n_kv_heads + kvh) * a.nsplit + split) * 4 * kPartial + h * kPartial;
-    if (c == 0) {
-      st_agent(dst, M);
-      st_agent(dst + 1, Lsum);
-    }
-    st_agent(dst + 4 + c, o);
+  for (int w = 0; w < NW; ++w) {
+    const Fin* f = wave_fin(sm, w);
+    const float sc = f->m[h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(f->m[h] - M);
+    Lsum += f->l[h] * sc;
+    o += f->o[h][c] * sc;
   }
+  if (tail) {
+    const float sc = sm.tfin.m[h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(sm.tfin.m[h] - M);
+    Lsum += sm.tfin.l[h] * sc;
+    o += sm.tfin.o[h][c] * sc;
+  }
+  float* dst = a.ws + ((int64_t(vb) * g.n_kv_heads + kvh) * a.nsplit + split) * 4 * kPartial + h * kPartial;
+  if (c == 0) {
+    st_agent(dst, M);
+    st_agent(dst + 1, Lsum);
+  }
+  st_agent(dst + 4 + c, o);
   // every thread's partial stores are complete (at the coherent level) before
   // the workgroup's counter increment; the last workgroup reads them after it
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1769,45 +1718,29 @@ __global__ __launch_bounds__((Plan<BASE, LH, LL, G>::NT)) void decode_kernel(Dec
 }
 
 template <int BASE, int LH, int LL, int G>
-int waves_of() { return Plan<BASE, LH, LL, G>::NW; }
-
-// the kernel needs 4 x 128 threads (one per query head and channel): level
-// pairs whose 8-wave workgroup does not fit the LDS are not built
-template <int BASE, int LH, int LL, int G>
-constexpr bool fits() { return Plan<BASE, LH, LL, G>::NT >= 4 * kD; }
-
-template <int BASE, int LH, int LL, int G>
 int occupancy() {
-  if constexpr (!fits<BASE, LH, LL, G>()) {
-    return 0;
-  } else {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, decode_kernel<BASE, LH, LL, G>, Plan<BASE, LH, LL, G>::NT, 0) != hipSuccess)
-      return 1;
-    return n > 0 ? n : 1;
-  }
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, decode_kernel<BASE, LH, LL, G>, Plan<BASE, LH, LL, G>::NT, 0) != hipSuccess)
+    return 1;
+  return n > 0 ? n : 1;
 }
 
 template <int BASE, int LH, int LL, int G>
 int launch_g(const DecodeArgs& a, hipStream_t st) {
-  if constexpr (!fits<BASE, LH, LL, G>()) {
-    return -2;
-  } else {
-    using PL = Plan<BASE, LH, LL, G>;
-    // slot s of stride = nsplit x NW holds tiles s, s + stride, ...: their
-    // number, all and of the high pool, without a division in every wave
-    DecodeArgs d = a;
-    const int stride = a.nsplit * PL::NW;
-    d.tiles[0] = int((a.n_rows[0] + kSlots - 1) / kSlots);
-    d.tiles[1] = d.tiles[0] + int((a.n_rows[1] + kSlots - 1) / kSlots);
-    for (int i = 0; i < 2; ++i) {
-      d.full[i] = d.tiles[i] / stride;
-      d.left[i] = d.tiles[i] % stride;
-    }
-    dim3 grid(a.nsplit, a.g.n_kv_heads, a.g.batch * a.n_layers_launched);
-    hipLaunchKernelGGL((decode_kernel<BASE, LH, LL, G>), grid, dim3(PL::NT), 0, st, d);
-    return hipGetLastError() == hipSuccess ? 0 : -5;
+  using PL = Plan<BASE, LH, LL, G>;
+  // slot s of stride = nsplit x NW holds tiles s, s + stride, ...: their
+  // number, all and of the high pool, without a division in every wave
+  DecodeArgs d = a;
+  const int stride = a.nsplit * PL::NW;
+  d.tiles[0] = int((a.n_rows[0] + kSlots - 1) / kSlots);
+  d.tiles[1] = d.tiles[0] + int((a.n_rows[1] + kSlots - 1) / kSlots);
+  for (int i = 0; i < 2; ++i) {
+    d.full[i] = d.tiles[i] / stride;
+    d.left[i] = d.tiles[i] % stride;
   }
+  dim3 grid(a.nsplit, a.g.n_kv_heads, a.g.batch * a.n_layers_launched);
+  hipLaunchKernelGGL((decode_kernel<BASE, LH, LL, G>), grid, dim3(PL::NT), 0, st, d);
+  return hipGetLastError() == hipSuccess ? 0 : -5;
 }
 
 template <int BASE, int LH, int LL>
@@ -1822,13 +1755,13 @@ int launch_dec(const DecodeArgs& a, hipStream_t st) {
 }
 
 template <int BASE, int LH, int LL>
-int occ_dec(int G, bool waves) {
+int occ_dec(int G) {
   if constexpr (BASE == 1) {
-    return waves ? waves_of<BASE, LH, LL, 128>() : occupancy<BASE, LH, LL, 128>();
+    return occupancy<BASE, LH, LL, 128>();
   } else {
-    if (G == 128) return waves ? waves_of<BASE, LH, LL, 128>() : occupancy<BASE, LH, LL, 128>();
-    if (G == 64) return waves ? waves_of<BASE, LH, LL, 64>() : occupancy<BASE, LH, LL, 64>();
-    return waves ? waves_of<BASE, LH, LL, 32>() : occupancy<BASE, LH, LL, 32>();
+    if (G == 128) return occupancy<BASE, LH, LL, 128>();
+    if (G == 64) return occupancy<BASE, LH, LL, 64>();
+    return occupancy<BASE, LH, LL, 32>();
   }
 }
 
@@ -1857,29 +1790,27 @@ int launch_decode(const DecodeArgs& a, hipStream_t s) {
   return -2;
 }
 
-static int decode_query(int base, int LH, int LL, int G, bool waves) {
-  if (base == 0 && LH == 6 && LL == 5) return occ_dec<0, 6, 5>(G, waves);
-  if (base == 0 && LH == 5 && LL == 4) return occ_dec<0, 5, 4>(G, waves);
-  if (base == 0 && LH == 6 && LL == 4) return occ_dec<0, 6, 4>(G, waves);
-  if (base == 0 && LH == 4 && LL == 3) return occ_dec<0, 4, 3>(G, waves);
-  if (base == 0 && LH == 5 && LL == 3) return occ_dec<0, 5, 3>(G, waves);
-  if (base == 0 && LH == 6 && LL == 3) return occ_dec<0, 6, 3>(G, waves);
-  if (base == 1 && LH == 4 && LL == 3) return occ_dec<1, 4, 3>(G, waves);
-  if (base == 2 && LH == 6 && LL == 5) return occ_dec<2, 6, 5>(G, waves);
-  if (base == 2 && LH == 5 && LL == 4) return occ_dec<2, 5, 4>(G, waves);
+int decode_blocks_per_cu(int base, int LH, int LL, int G) {
+  if (base == 0 && LH == 6 && LL == 5) return occ_dec<0, 6, 5>(G);
+  if (base == 0 && LH == 5 && LL == 4) return occ_dec<0, 5, 4>(G);
+  if (base == 0 && LH == 6 && LL == 4) return occ_dec<0, 6, 4>(G);
+  if (base == 0 && LH == 4 && LL == 3) return occ_dec<0, 4, 3>(G);
+  if (base == 0 && LH == 5 && LL == 3) return occ_dec<0, 5, 3>(G);
+  if (base == 0 && LH == 6 && LL == 3) return occ_dec<0, 6, 3>(G);
+  if (base == 1 && LH == 4 && LL == 3) return occ_dec<1, 4, 3>(G);
+  if (base == 2 && LH == 6 && LL == 5) return occ_dec<2, 6, 5>(G);
+  if (base == 2 && LH == 5 && LL == 4) return occ_dec<2, 5, 4>(G);
   if (G == 128) {
-    if (base == 0 && LH == 8 && LL == 7) return waves ? waves_of<0, 8, 7, 128>() : occupancy<0, 8, 7, 128>();
-    if (base == 0 && LH == 7 && LL == 6) return waves ? waves_of<0, 7, 6, 128>() : occupancy<0, 7, 6, 128>();
-    if (base == 0 && LH == 3 && LL == 2) return waves ? waves_of<0, 3, 2, 128>() : occupancy<0, 3, 2, 128>();
-    if (base == 2 && LH == 8 && LL == 7) return waves ? waves_of<2, 8, 7, 128>() : occupancy<2, 8, 7, 128>();
-    if (base == 2 && LH == 7 && LL == 6) return waves ? waves_of<2, 7, 6, 128>() : occupancy<2, 7, 6, 128>();
-    if (base == 2 && LH == 3 && LL == 2) return waves ? waves_of<2, 3, 2, 128>() : occupancy<2, 3, 2, 128>();
+    if (base == 0 && LH == 8 && LL == 7) return occupancy<0, 8, 7, 128>();
+    if (base == 0 && LH == 7 && LL == 6) return occupancy<0, 7, 6, 128>();
+    if (base == 0 && LH == 3 && LL == 2) return occupancy<0, 3, 2, 128>();
+    if (base == 2 && LH == 8 && LL == 7) return occupancy<2, 8, 7, 128>();
+    if (base == 2 && LH == 7 && LL == 6) return occupancy<2, 7, 6, 128>();
+    if (base == 2 && LH == 3 && LL == 2) return occupancy<2, 3, 2, 128>();
   }
-  return waves ? 8 : 1;
+  return 1;
 }
 
-int decode_blocks_per_cu(int base, int LH, int LL, int G) { return decode_query(base, LH, LL, G, false); }
-int decode_waves(int base, int LH, int LL, int G) { return decode_query(base, LH, LL, G, true); }
 
 }  // namespace semkv
 

@@ -113,11 +113,12 @@ int64_t decode_slots(const semkv_config& k) {
 }
 
 // Records on the busiest SIMD when a unit's nt tiles are dealt to ns
-// workgroups of nw waves: slot s = wave * ns + split takes tiles s, s +
+// workgroups of nw waves (kDecodeWaves): slot s = wave * ns + split takes tiles s, s +
 // stride, ... (stride = ns * nw), so slot s holds full + (s < left) tiles
 // (full = nt div stride, left = nt mod stride); waves w and w + nw/2 share a
 // SIMD, and the SIMD of split 0's waves 0 and nw/2 holds the most.
-int64_t busiest_simd(int64_t nt, int64_t ns, int nw) {
+int64_t busiest_simd(int64_t nt, int64_t ns) {
+  constexpr int nw = kDecodeWaves;
   const int64_t stride = ns * nw, full = nt / stride, left = nt % stride;
   return 2 * full + (left > 0) + (left > ns * (nw / 2));
 }
@@ -136,13 +137,12 @@ int plan(const semkv_cache* c, int n_tail, int layers = 1) {
   if (nt == 0) return n_tail > 0 ? 1 : 0;
   const int64_t units = int64_t(c->cfg.batch) * c->cfg.n_kv_heads * layers;
   int64_t ns_max = decode_slots(c->cfg) / units;
-  const int nw = decode_waves(c->cfg.base, c->cfg.L_hi, c->cfg.L_lo, c->cfg.group);
   if (ns_max > nt) ns_max = nt;                  // every workgroup holds a tile
   if (ns_max > kMaxSplits / layers) ns_max = kMaxSplits / layers;
   if (ns_max < 1) ns_max = 1;
-  int64_t best = ns_max, best_load = busiest_simd(nt, ns_max, nw);
+  int64_t best = ns_max, best_load = busiest_simd(nt, ns_max);
   for (int64_t ns = ns_max - 1; ns >= 1; --ns) {
-    const int64_t load = busiest_simd(nt, ns, nw);
+    const int64_t load = busiest_simd(nt, ns);
     if (load < best_load) {
       best = ns;
       best_load = load;
@@ -271,9 +271,6 @@ int semkv_cache_sizes(const semkv_config* cfg, semkv_sizes* out) {
   if (k.base != SEMKV_BASE_TQ && k.group != 32 && k.group != 64 && k.group != 128) return SEMKV_EUNSUPPORTED;
   if (k.base == SEMKV_BASE_TQ && k.group != 128) return SEMKV_EUNSUPPORTED;
   if (grid_pair(k.L_hi, k.L_lo) && k.group != 128) return SEMKV_EUNSUPPORTED;
-  // the decode kernel needs one 8-wave workgroup's tables and buffers in a
-  // compute unit's LDS (every supported pair's does)
-  if (decode_waves(k.base, k.L_hi, k.L_lo, k.group) < 8) return SEMKV_EUNSUPPORTED;
   memset(out, 0, sizeof(*out));
   int64_t khi = top_count(k.max_prompt, k.r_num, k.r_den);
   int64_t hi_rows = khi + k.max_new, lo_rows = k.max_prompt - khi + k.max_new;

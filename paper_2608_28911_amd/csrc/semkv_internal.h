@@ -111,6 +111,7 @@ constexpr int kPartial = 132;  // m, l, 2 pad, o[128]
 // units do not queue their atomics on one line
 constexpr int kCounterStride = 64;
 constexpr int kMaxSplits = 256;   // splits per (sequence, kv head)
+constexpr int kDecodeWaves = 8;   // waves of a decode workgroup
 // buffer descriptor word 3 of a raw buffer of 32-bit elements (gfx9 family)
 constexpr int kBufferWord3 = 0x00020000;
 
@@ -141,9 +142,7 @@ int launch_dequant(const DequantArgs& a, hipStream_t s);
 int launch_decode(const DecodeArgs& a, hipStream_t s);
 int launch_score_hidden(const HiddenArgs& a, hipStream_t s);
 int launch_kv_norm(const KvNormArgs& a, hipStream_t s);
-// decode workgroups one compute unit holds at once for this cache's kernel,
-// and the waves of one such workgroup (a wave takes every NW-th tile of a run)
+// decode workgroups one compute unit holds at once for this cache's kernel
 int decode_blocks_per_cu(int base, int L_hi, int L_lo, int G);
-int decode_waves(int base, int L_hi, int L_lo, int G);
 
 }  // namespace semkv
