@@ -15,11 +15,15 @@
 // 301 and 42 %.  A segment's registers are loaded again as soon as it is
 // decoded, which keeps a wave's loads spread over its record: all at the
 // record's top, batch 1 at 32768 tokens took 13.8 us a launch instead of 13.2
-// and tq at 131072 25.1 instead of 24.0.  Measured from the staged form: batch
-// 16 at 16384 tokens 48.0 -> 42.6 us a launch, batch 4 at 32768 31.6 -> 28.0,
-// tq at 131072 25.8 -> 24.0, batch 1 at 32768 14.2 -> 13.2.  What is left is
-// mostly the launch's fixed part -- 2.6 us to launch, 2.7 of prologue, 4 of
-// merge -- and memory: at batch 16 the records stream at about 5.6 TB/s.)
+// and tq at 131072 25.1 instead of 24.0.  The staged form against this one, in
+// a graph on one box, us a launch: batch 16 at 16384 tokens 46.5 -> 40.9, batch
+// 4 at 32768 with a tail 30.5 -> 27.1, tq at 131072 25.5 -> 23.3, batch 1 at
+// 32768 14.0 -> 12.7, 2048 tokens 10.1 -> 9.9.  The prologue is longer for it,
+// 3.0 us instead of 2.4 until the operands are ready (tq 3.4 instead of 3.0),
+// but no wait for the first record follows, which ends at 5.5 instead of 6.3.
+// What is left is mostly the launch's fixed part -- 2.6 us to launch, 3.0 of
+// prologue, 4 of merge -- and memory: at batch 16 the records stream at about
+// 5.6 TB/s.)
 // Products run on the int8 matrix cores
 // (v_mfma_i32_16x16x64_i8), exact in their integer sums.  Per record:
 //   scores  C[16 rows (head, byte) x 16 tokens] += A B: A holds the query of

@@ -129,9 +129,15 @@ int64_t busiest_simd(int64_t nt, int64_t ns) {
 // those split counts, the one that leaves the busiest SIMD the fewest
 // records, and of equals the largest (the most compute units at work; a short
 // context then leaves some waves without a record rather than giving one
-// SIMD a record more).  The fp16 tail rides with the last workgroup.  0:
-// nothing cached.  A launch of `layers` layers plans over all their units
-// together.
+// SIMD a record more).  The largest against the smallest of equals, 6/5 levels,
+// 8 kv heads, us a launch: without a tail the smaller merge is 0.1-0.2 faster
+// at batch 1 up to 6000 tokens (2048: 8.87 / 8.65) and otherwise the larger by
+// up to 0.4 (batch 4, 8192 tokens: 12.4 / 12.8); with 37 tail rows, which the
+// last workgroup takes after its records, the larger by up to 1.3 (batch 2,
+// 8192 tokens: 11.9 / 13.2; batch 4, 4096: 12.1 / 13.2).  Over batches 1, 2, 4
+// and eight contexts from 1500 to 8192 tokens, 1 % for the largest.  The fp16
+// tail rides with the last workgroup.  0: nothing cached.  A launch of `layers`
+// layers plans over all their units together.
 int plan(const semkv_cache* c, int n_tail, int layers = 1) {
   const int64_t nt = (c->n_hi + kSlots - 1) / kSlots + (c->n_lo + kSlots - 1) / kSlots;
   if (nt == 0) return n_tail > 0 ? 1 : 0;
