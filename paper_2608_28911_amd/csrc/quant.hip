@@ -454,8 +454,9 @@ __device__ inline int quarter_of_thread(int tid) { return BASE == 0 ? tid & 3 : 
 // row of the code array (zeros for a row that is not there) and the metadata
 // of its share of the groups.  m: the rotating bases' sign masks.  bad: a value
 // was not finite.  GC: the rotated affine base's group size, 0 to read it from g.
+// Returns the tq base's norm (fp16 bits).
 template <int BASE, int L, int GC>
-__device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid, int q, const uint32_t m[16],
+__device__ uint16_t quantize_row(const PoolGeom& g, const uint16_t* src, bool valid, int q, const uint32_t m[16],
                              const float* tau, uint8_t* codes, uint8_t* meta_dst, int slot, bool& bad) {
   if constexpr (BASE == 0) {
     uint32_t d[16], code[8];
@@ -470,12 +471,14 @@ __device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid,
     uint32_t* dst = reinterpret_cast<uint32_t*>(codes + 32 * q);
 #pragma unroll
     for (int i = 0; i < 8; ++i) dst[i] = valid ? code[i] : 0u;
+    return 0;
   } else {
     float u[32];
     uint32_t code[8];
+    uint16_t r = 0;
     load_signed(src, valid, m, u);
     if constexpr (BASE == 1) {
-      const uint16_t r = tq_row<L>(u, tau, code);
+      r = tq_row<L>(u, tau, code);
       if (q == 0) reinterpret_cast<uint16_t*>(meta_dst)[slot] = valid ? r : uint16_t(0);
     } else {
       rotate_row(u);
@@ -498,6 +501,32 @@ __device__ void quantize_row(const PoolGeom& g, const uint16_t* src, bool valid,
       const int q0 = k >> 2, q1 = (k >> 1) & 1;
       dst[(64 * q1 + 32 * q0) / 4 + (k & 1)] = valid ? code[k] : 0u;
     }
+    return r;
+  }
+}
+
+// K's and V's row quarters of a tq row.  A norm that is a NaN is stored with the
+// row's own sign rather than the sign mask's: the row is read again where it is
+// reported as not finite, which brings all four of its lanes there, so nothing
+// is held in registers, and no branch is taken, for other rows.
+template <int L>
+__device__ inline void quantize_tq_rows(const PoolGeom& g, const uint16_t* k, const uint16_t* v, bool valid, int q, const uint32_t m[16],
+                                        const float* tau, uint8_t* ck, uint8_t* cv, uint8_t* meta, int slot) {
+  const uint16_t* const src[2] = {k, v};
+  uint16_t norm[2];
+  bool bad = false;
+#pragma unroll
+  for (int kv = 0; kv < 2; ++kv)
+    norm[kv] = quantize_row<1, L, 0>(g, src[kv], valid, q, m, tau, kv ? cv : ck, meta + kv * g.meta_bytes, slot, bad);
+  if (!(bad && valid)) return;
+  atomicOr(g.status, 2);
+  for (int kv = 0; kv < 2; ++kv) {
+    if ((norm[kv] & 0x7FFFu) <= 0x7C00u) continue;
+    const uint32_t plain[16] = {};
+    float x[32];
+    load_signed(src[kv], true, plain, x);
+    const uint16_t r = sqrt_f16(row_square_sum(x));
+    if (q == 0) reinterpret_cast<uint16_t*>(meta + kv * g.meta_bytes)[slot] = r;
   }
 }
 
@@ -669,10 +698,14 @@ __device__ void prefill_record(const QuantArgs& a, Lds& s, int pool, int tile, i
   for (int i = tid; i < kMaxBodyWords + 8; i += 256) s.bk[i] = s.bv[i] = 0u;
   bool bad = false;
   const int64_t base_off = int64_t(l) * a.sL + int64_t(b) * a.sB + int64_t(h) * a.sH + int64_t(tok) * a.sT + 32 * q;
+  if constexpr (BASE == 1) {
+    quantize_tq_rows<L>(g, a.K + base_off, a.V + base_off, valid, q, m, g.tau[pool], s.ck + r * kPitch, s.cv + r * kPitch, rec + 2 * tb, r);
+  } else {
 #pragma unroll
-  for (int kv = 0; kv < 2; ++kv)
-    quantize_row<BASE, L, GC>(g, (kv ? a.V : a.K) + base_off, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
-                          rec + 2 * tb + kv * g.meta_bytes, r, bad);
+    for (int kv = 0; kv < 2; ++kv)
+      quantize_row<BASE, L, GC>(g, (kv ? a.V : a.K) + base_off, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
+                                rec + 2 * tb + kv * g.meta_bytes, r, bad);
+  }
   if (bad && valid) atomicOr(g.status, 2);
   __syncthreads();
   pack_record<L>(s.ck, s.cv, s.bk, s.bv);
@@ -732,10 +765,14 @@ __device__ void close_record(const CloseArgs& a, Lds& s, const int* row_of, int 
     const uint16_t* src = a.tail + ((((int64_t(b) * g.n_layers + l) * g.n_kv_heads + h) * 2) * kSlots + row) * kD + 32 * q;
     uint32_t m[16];
     if constexpr (BASE != 0) sign_masks(g.signs[(int64_t(l) * g.n_kv_heads + h) * 4 + q], m);
+    if constexpr (BASE == 1) {
+      quantize_tq_rows<L>(g, src, src + kSlots * kD, valid, q, m, g.tau[pool], s.ck + r * kPitch, s.cv + r * kPitch, rec + 2 * tb, r);
+    } else {
 #pragma unroll
-    for (int kv = 0; kv < 2; ++kv)
-      quantize_row<BASE, L, 0>(g, src + kv * kSlots * kD, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
-                            rec + 2 * tb + kv * g.meta_bytes, r, bad);
+      for (int kv = 0; kv < 2; ++kv)
+        quantize_row<BASE, L, 0>(g, src + kv * kSlots * kD, valid, q, m, g.tau[pool], (kv ? s.cv : s.ck) + r * kPitch,
+                                 rec + 2 * tb + kv * g.meta_bytes, r, bad);
+    }
   }
   if (bad && valid) atomicOr(g.status, 2);
   __syncthreads();

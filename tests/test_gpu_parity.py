@@ -366,6 +366,34 @@ def test_affine_code_ties_round_to_even(G):
         assert np.array_equal(U.gpu_records(cache, 0, 0, 0, p, u.count(p)), u.records(p)), "pool %d" % p
 
 
+def test_turboquant_norm_of_rows_that_are_not_finite():
+    """A row's stored norm carries the NaN the row holds (quieted), whatever the
+    sign mask does to its channel; a row with an infinity saturates at 65504."""
+    import torch
+    cfgw = get_config(4, n_layers=1, n_kv_heads=1, n_q_heads=4, r_num=1, r_den=2)
+    T = 128                                              # one full record in each pool
+    rng = np.random.default_rng(17)
+    pats = np.array([0x7E00, 0xFE00, 0x7C01, 0x7FFF, 0xFC01, 0xFE23, 0x7C00, 0xFC00], np.uint16)
+    want = np.array([0x7E00, 0xFE00, 0x7E01, 0x7FFF, 0xFE01, 0xFE23, 0x7BFF, 0x7BFF], np.uint16)
+    X = rng.standard_normal((2, T, 128)).astype(np.float16)
+    for t in range(T):
+        X.view(np.uint16)[:, t, rng.permutation(128)[:2]] = np.where(pats[t % 8] & 0x3FF, pats[t % 8], [pats[t % 8], 0x3C00])
+    cache = U.make_cache(cfgw, T, n_layers=1, max_new=8)
+    s = np.arange(T, 0, -1, dtype=np.float32)[None]      # the first half is the high pool
+    U.prefill(cache, cfgw, T, scores=s, kv=lambda l: (X[0][None, None], X[1][None, None]))
+    for i in range(8):                                   # and a residual block: rows 0-3 to the high pool
+        cache.append_kv(0, *(torch.from_numpy(X[kv, i].copy()).cuda()[None, None] for kv in range(2)))
+        cache.append_commit(torch.tensor([float(-i)], device="cuda"))
+    cache.flush()
+    assert cache.status() == 2
+    for pool, tb, n in ((0, cache.sz.tile_bytes_hi, slice(0, 4)), (1, cache.sz.tile_bytes_lo, slice(4, 8))):
+        rec = U.gpu_records(cache, 0, 0, 0, pool, 128).reshape(2, -1)
+        for kv in range(2):
+            got = rec[:, 2 * tb + 128 * kv:2 * tb + 128 * (kv + 1)].copy().view(np.uint16)
+            assert np.array_equal(got[0], np.tile(want, 8)), "pool %d %s" % (pool, "KV"[kv])
+            assert np.array_equal(got[1, :4], want[n]) and not got[1, 4:].any(), "closed block, pool %d %s" % (pool, "KV"[kv])
+
+
 def test_status_word_reports_nan_and_inf():
     import torch
     cfgw = get_config(0, n_kv_heads=1, n_q_heads=4)
